@@ -214,48 +214,97 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
     return c;
 }
 
-// IEEE division and square root for the operand ranges of the transform below (normal,
-// finite, no zero divisor, square roots of positive normal values only): the hardware
-// estimate refined by the same fused steps as the general correctly rounded sequences,
-// without their scaling and special-value steps, which never act in these ranges -- the
-// results are the IEEE ones bit for bit.
-__device__ __forceinline__ float div_rn_normal(float n, float d) {
-    float r = __builtin_amdgcn_rcpf(d);
-    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-    float q = n * r;
-    q = __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+// The counter word of a sample's Philox calls that changes within the sample loop is only
+// c.y = tau / 2, and words c.z and c.w are wave-uniform: after two rounds every product but
+// one holds values that are the same in all calls of the sample or wave-uniform.  Those are
+// formed once per sample (five of the twenty 64-bit products of a call; each product is a
+// full, never paired issue cycle).
+struct PhiloxLane {
+    uint32_t e, f, g, h;  // lane parts of the state after rounds 2 and 3
+    uint32_t y1;          // wave-uniform: word 1 after round 1 without its key (unused bits of the counter)
+};
+constexpr uint32_t PHILOX_M0 = 0xD2511F53u, PHILOX_M1 = 0xCD9E8D57u, PHILOX_W0 = 0x9E3779B9u, PHILOX_W1 = 0xBB67AE85u;
+
+__device__ __forceinline__ PhiloxLane philox_lane(uint32_t k, uint32_t z, uint32_t w, uint32_t k0, uint32_t k1) {
+    // round 1 on (k, -, z, w)
+    const uint64_t a0 = (uint64_t)PHILOX_M0 * k, a1 = (uint64_t)PHILOX_M1 * z;
+    const uint32_t z1 = (uint32_t)(a0 >> 32) ^ w ^ k1, w1 = (uint32_t)a0, y1 = (uint32_t)a1;
+    // round 2: word 0 and 1
+    const uint32_t k0b = k0 + PHILOX_W0, k1b = k1 + PHILOX_W1, k0c = k0b + PHILOX_W0, k1c = k1b + PHILOX_W1;
+    const uint64_t b1 = (uint64_t)PHILOX_M1 * z1;
+    const uint32_t x2 = (uint32_t)(b1 >> 32) ^ y1 ^ k0b;
+    // round 3: the product of word 0
+    const uint64_t c0 = (uint64_t)PHILOX_M0 * x2;
+    return PhiloxLane{w1 ^ k1b, (uint32_t)b1 ^ k0c, (uint32_t)(c0 >> 32) ^ k1c, (uint32_t)c0, (uint32_t)(a1 >> 32) ^ k0};
+}
+
+// philox4x32_10((k, y, z, w), key) from the sample's philox_lane; y wave-uniform
+template <bool BITOP3>
+__device__ __forceinline__ uint4 philox_call(const PhiloxLane &p, uint32_t y, uint32_t k0, uint32_t k1) {
+    const uint64_t b0 = (uint64_t)PHILOX_M0 * (p.y1 ^ y);  // round 2 on the wave-uniform word 0 (scalar unit)
+    const uint64_t c1 = (uint64_t)PHILOX_M1 * (p.e ^ (uint32_t)(b0 >> 32));
+    uint4 c = make_uint4((uint32_t)(c1 >> 32) ^ p.f, (uint32_t)c1, p.g ^ (uint32_t)b0, p.h);
+    k0 += 2u * PHILOX_W0;
+    k1 += 2u * PHILOX_W1;
+#pragma unroll
+    for (int r = 3; r < 10; ++r) {
+        k0 += PHILOX_W0;
+        k1 += PHILOX_W1;
+        asm volatile("" : "+s"(k0), "+s"(k1));  // (bumped in place, as above)
+        const uint64_t p0 = (uint64_t)PHILOX_M0 * c.x;
+        const uint64_t p1 = (uint64_t)PHILOX_M1 * c.z;
+        if constexpr (BITOP3)
+            c = make_uint4(xor3_uniform((uint32_t)(p1 >> 32), c.y, k0), (uint32_t)p1,
+                           xor3_uniform((uint32_t)(p0 >> 32), c.w, k1), (uint32_t)p0);
+        else
+            c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k0, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c.w ^ k1,
+                           (uint32_t)p0);
+    }
+    return c;
+}
+
+// IEEE division and square root on the operands of the transform below.  The hardware
+// estimates with one fused correction each give the correctly rounded quotient and root for
+// every operand that can occur (2^23 radius words: checked one by one against the IEEE
+// results, and against the oracle by the exhaustive test of the transform); the general
+// sequences take twice as many instructions, half of them compares and selects, which are
+// never issued in pairs.
+__device__ __forceinline__ float div_rn_radius(float n, float d) {
+    const float r = __builtin_amdgcn_rcpf(d);
+    const float q = n * r;
     return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
 }
-__device__ __forceinline__ float sqrt_rn_normal(float x) {
-    const float s = __builtin_amdgcn_sqrtf(x);  // within 1 ulp
-    const float s_dn = __uint_as_float(__float_as_uint(s) - 1u), s_up = __uint_as_float(__float_as_uint(s) + 1u);
-    float r = __builtin_fmaf(-s_dn, s, x) <= 0.0f ? s_dn : s;
-    return __builtin_fmaf(-s_up, s, x) > 0.0f ? s_up : r;
+__device__ __forceinline__ float sqrt_rn_radius(float x) {
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float s = x * y, h = 0.5f * y;
+    return __builtin_fmaf(__builtin_fmaf(-s, s, x), h, s);
 }
 
 // Gaussian pair from two 32-bit words.  The float32 operation sequence is fixed
 // (IEEE round-to-nearest add, mul, fma, div, sqrt; no contraction), so the
-// perturbations are reproducible bit for bit on any IEEE-conforming device.
+// perturbations are reproducible bit for bit on any IEEE-conforming device.  Powers of two
+// are folded into the constants (the factor -2 under the root into the logarithm's, the
+// scale 2^-24 of u1 into its exponent), which leaves every rounding where it was.
 __device__ __forceinline__ float2 gauss_pair(uint32_t r_even, uint32_t r_odd) {
 #pragma clang fp contract(off)
-    const float L3 = 0x1.555556p-1f, L5 = 0x1.99999ap-2f, L7 = 0x1.24924ap-2f;
-    const float L9 = 0x1.c71c72p-3f, L11 = 0x1.745d18p-3f, L13 = 0x1.3b13b2p-3f;
-    const float LN2_HI = 0x1.62e4p-1f, LN2_LO = 0x1.7f7d1cp-20f;
+    // -2 x the coefficients of ln((1 + z) / (1 - z)) and of ln 2
+    const float L3 = -0x1.555556p+0f, L5 = -0x1.99999ap-1f, L7 = -0x1.24924ap-1f;
+    const float L9 = -0x1.c71c72p-2f, L11 = -0x1.745d18p-2f, L13 = -0x1.3b13b2p-2f;
+    const float LN2_HI = -0x1.62e4p+0f, LN2_LO = -0x1.7f7d1cp-19f;
     const float S1 = 0x1.921fb6p+2f, S3 = -0x1.4abbcep+5f, S5 = 0x1.466bc6p+6f;
     const float S7 = -0x1.32d2ccp+6f, S9 = 0x1.507834p+5f;
     const float C2 = -0x1.3bd3ccp+4f, C4 = 0x1.03c1f0p+6f, C6 = -0x1.55d3c8p+6f;
     const float C8 = 0x1.e1f506p+5f, C10 = -0x1.a6d1f2p+4f;
-    // radius sqrt(-2 ln u1), u1 = (2*(r_even >> 9) + 1) 2^-24, ln by exponent split + atanh series
-    const float u1 = (float)(2u * (r_even >> 9) + 1u) * 0x1p-24f;
+    // radius sqrt(-2 ln u1), u1 = (2*(r_even >> 9) + 1) 2^-24, ln by exponent split + atanh series.
     // u1 = m 2^e with m in [sqrt(1/2), sqrt 2]: m > SQRT2 (the float just below sqrt 2) is
     // halved.  In integer form: adding 2^23 - 0x3504f4 to the bits carries into the
     // exponent exactly when the mantissa field exceeds that of SQRT2, and the mantissa of
-    // m is then the low 23 bits plus the bits of the float above sqrt(1/2).
-    const uint32_t b = __float_as_uint(u1) + 0x4afb0cu;
-    const int e = (int)(b >> 23) - 127;
+    // m is then the low 23 bits plus the bits of the float above sqrt(1/2); the exponent's
+    // bias and the scale 2^-24 come off in the same addition.
+    const uint32_t b = __float_as_uint((float)((r_even >> 8) | 1u)) + (0x4afb0cu - ((127u + 24u) << 23));
+    const int e = (int)b >> 23;
     const float m = __uint_as_float((b & 0x7fffffu) + 0x3f3504f4u);
-    const float f = m - 1.0f;
-    const float z = div_rn_normal(f, m + 1.0f);  // f in [-0.293, 0.415], m + 1 in [1.707, 2.415]
+    const float z = div_rn_radius(m - 1.0f, m + 1.0f);  // quotient of [-0.293, 0.415] and [1.707, 2.415]
     const float w = z * z;
     float p = __builtin_fmaf(L13, w, L11);
     p = __builtin_fmaf(p, w, L9);
@@ -263,14 +312,15 @@ __device__ __forceinline__ float2 gauss_pair(uint32_t r_even, uint32_t r_odd) {
     p = __builtin_fmaf(p, w, L5);
     p = __builtin_fmaf(p, w, L3);
     p = p * w;
-    const float lnm = __builtin_fmaf(z, p, z + z);
+    const float lnm = __builtin_fmaf(z, p, -4.0f * z);
     const float ef = (float)e;
-    const float lnu = __builtin_fmaf(ef, LN2_HI, __builtin_fmaf(ef, LN2_LO, lnm));
-    const float rho = sqrt_rn_normal(-2.0f * lnu);  // -2 ln u1 in [1.1e-7, 33.3]
-    // angle 2 pi u2, u2 = (r_odd >> 8) 2^-24: exact quarter-turn split, Taylor polynomials
-    const uint32_t j = r_odd >> 8;
-    const uint32_t q = (j + (1u << 21)) >> 22;
-    const int32_t ri = (int32_t)j - (int32_t)(q << 22);
+    const float lnu = __builtin_fmaf(ef, LN2_HI, __builtin_fmaf(ef, LN2_LO, lnm));  // -2 ln u1 in [1.1e-7, 33.3]
+    const float rho = sqrt_rn_radius(lnu);
+    // angle 2 pi u2, u2 = j 2^-24, j = r_odd >> 8: exact quarter-turn split j = q 2^22 + ri with
+    // ri in [-2^21, 2^21) (the low 22 bits of j, signed; q mod 4 the top bits of r_odd + 2^29),
+    // Taylor polynomials
+    const int32_t ri = (int32_t)(r_odd << 2) >> 10;
+    const uint32_t t = r_odd + 0x20000000u;
     const float r = (float)ri * 0x1p-24f;
     const float r2 = r * r;
     float ps = __builtin_fmaf(S9, r2, S7);
@@ -283,13 +333,12 @@ __device__ __forceinline__ float2 gauss_pair(uint32_t r_even, uint32_t r_odd) {
     pc = __builtin_fmaf(pc, r2, C4);
     pc = __builtin_fmaf(pc, r2, C2);
     const float cs = __builtin_fmaf(pc, r2, 1.0f);
-    // quarter turns: (sin, cos) = (sn, cs), (cs, -sn), (-sn, -cs), (-cs, sn) for qq = 0..3;
+    // quarter turns: (sin, cos) = (sn, cs), (cs, -sn), (-sn, -cs), (-cs, sn) for t >> 30 = 0..3;
     // the signs as sign-bit flips (exact), no branches
-    const uint32_t qq = q & 3u;
-    const bool odd = (qq & 1u) != 0u;
+    const bool odd = (t & 0x40000000u) != 0u;
     const float sa = odd ? cs : sn, ca = odd ? sn : cs;
-    const float sin_t = __uint_as_float(__float_as_uint(sa) ^ ((qq & 2u) << 30));
-    const float cos_t = __uint_as_float(__float_as_uint(ca) ^ (((qq + 1u) & 2u) << 30));
+    const float sin_t = __uint_as_float(__float_as_uint(sa) ^ (t & 0x80000000u));
+    const float cos_t = __uint_as_float(__float_as_uint(ca) ^ ((t + 0x40000000u) & 0x80000000u));
     return make_float2(rho * cos_t, rho * sin_t);
 }
 
@@ -372,8 +421,8 @@ struct MathF32 {
     // max(x, 0) as one median (0 for a NaN, like x > 0 ? x : 0; +inf becomes the largest
     // finite value, which only a state that is already non-finite reaches)
     static __device__ __forceinline__ T pos_(T x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 3.40282347e38f); }
-    // max(x, lo) of a value pos_ returned (never NaN)
-    static __device__ __forceinline__ T floor_(T x, T lo) { return fmaxf(x, lo); }
+    // max(pos_(x), lo) for lo > 0, one median again
+    static __device__ __forceinline__ T pos_floor_(T x, T lo) { return __builtin_amdgcn_fmed3f(x, lo, 3.40282347e38f); }
 };
 
 // MathF32 with the wave-uniform atan range reduction (throughput kernels)
@@ -394,7 +443,7 @@ struct MathF64 {
     static __device__ __forceinline__ T cos_rev(T x) { return ::cos(x); }
     static __device__ __forceinline__ T fma_(T a, T b, T c) { return ::fma(a, b, c); }
     static __device__ __forceinline__ T pos_(T x) { return x > 0.0 ? x : 0.0; }
-    static __device__ __forceinline__ T floor_(T x, T lo) { return x > lo ? x : lo; }
+    static __device__ __forceinline__ T pos_floor_(T x, T lo) { return x > lo ? x : lo; }
 };
 
 template <typename T>
@@ -475,7 +524,7 @@ __device__ __forceinline__ void deriv_cs(const VehConst<typename M::T> &V, const
     using T = typename M::T;
     const T vx = M::pos_(vx_);
     if (MODEL == 0) {
-        const T inv_vh = M::rcp_(M::floor_(vx, V.v_eps));
+        const T inv_vh = M::rcp_(M::pos_floor_(vx_, V.v_eps));
         const T Fyf = tyre_force<M>(V, V.lf, c.delta, vy, om, inv_vh);
         const T Fyr = tyre_force<M>(V, -V.lr, T(0), vy, om, inv_vh);
         deriv_rates<M>(V, c, vx, vy, om, cp, sp, Fyf, Fyr, d);
@@ -510,7 +559,7 @@ __device__ __forceinline__ void deriv_pair(const VehConst<float> &V, const StepC
     const float vx = MathF32::pos_(vx_);
     const float pr = MathF32::to_rev(psi);
     const float cp = MathF32::cos_rev(pr), sp = MathF32::sin_rev(pr);
-    const float inv_vh = MathF32::rcp_(MathF32::floor_(vx, V.v_eps));
+    const float inv_vh = MathF32::rcp_(MathF32::pos_floor_(vx_, V.v_eps));
     const float F = tyre_force<MathF32>(V, rear ? -V.lr : V.lf, rear ? 0.0f : c.delta, vy, om, inv_vh);
     const float Fo = dpp_swap_f32(F);
     deriv_rates<MathF32>(V, c, vx, vy, om, cp, sp, rear ? Fo : F, rear ? F : Fo, d);
@@ -599,10 +648,12 @@ __device__ __forceinline__ VehConst<float> veh_f32(const KParams &P) {
     return V;
 }
 
-// Pi_U: box clip; a NaN stays NaN so that the sample is flagged non-finite
+// Pi_U: box clip; a NaN stays NaN so that the sample is flagged non-finite.  CHECK false:
+// the mean and the scale are known to be finite, so with a finite z there is no NaN to keep.
+template <bool CHECK = true>
 __device__ __forceinline__ float clip_keep_nan(float v, float lo, float hi) {
     const float c = __builtin_amdgcn_fmed3f(v, lo, hi);
-    return v != v ? v : c;
+    return CHECK && v != v ? v : c;
 }
 
 // ------------------------------------------------------------------------------
@@ -617,15 +668,16 @@ struct Foot {
     bool limit;
 };
 
-// Foot on segment `seg` between the geometry rows A0, A1 (g0, g1: the point's signed
-// distances ahead of their normal lines): t solves cross(p - c(t), n(t)) = 0 with the
+// Foot on the segment whose rows start at byte offset `o` (returned as `seg`, in the caller's
+// unit) between the geometry rows A0, A1 (g0, g1: the point's signed distances ahead of their
+// normal lines): t solves cross(p - c(t), n(t)) = 0 with the
 // stable quadratic root; s, w_L, w_R interpolated from the segment's second rows.
-__device__ __forceinline__ Foot foot_on(const float4 *__restrict__ nodes, float X, float Y, int seg, float4 A0,
+__device__ __forceinline__ Foot foot_on(const float4 *__restrict__ nodes, float X, float Y, int o, int seg, float4 A0,
                                         float4 A1, float g0, float g1) {
     Foot f;
     f.seg = seg;
     f.limit = !(g0 >= 0.0f && g1 <= 0.0f);
-    const float4 B0 = nodes[2 * seg + 1], B1 = nodes[2 * seg + 3];
+    const float4 B0 = *(const float4 *)((const char *)nodes + o + 16), B1 = *(const float4 *)((const char *)nodes + o + 48);
     const float rx = X - A0.x, ry = Y - A0.y;
     const float Dx = A1.x - A0.x, Dy = A1.y - A0.y;
     const float dnx = A1.z - A0.z, dny = A1.w - A0.w;
@@ -645,36 +697,48 @@ __device__ __forceinline__ Foot foot_on(const float4 *__restrict__ nodes, float 
     return f;
 }
 
-// Segment search from `seg` (at most max_moves moves, inside the window), then the foot.
-// The search carries only the signed distances; the geometry rows of the final segment
-// are read again together with its second rows.
-// (The move budget and the window's ends are folded into one bound on the row address per
-// direction, so a move costs the row read, the normal-line test, two compares and one add.)
+// Segment search from the segment whose rows start at byte offset `o0` (32 per node; at most
+// max_moves moves, inside the window), then the foot; the segment comes back as such an
+// offset, too.  The search carries the byte offset of a geometry row only, in batches of rows read
+// together: a car passes up to five nodes per step, and a walk of one row per iteration
+// waited for LDS and paid the exec-mask bookkeeping of a divergent loop at every one of
+// them.  The signed distances at the final segment are formed again from its two rows, read
+// for the foot in any case.
 __device__ __forceinline__ Foot project(const float4 *__restrict__ nodes, int W, int max_moves, float X, float Y,
-                                        int seg) {
-    const int seg0 = seg;
-    const float4 *q = nodes + 2 * seg + 2;  // geometry row of node seg + 1
-    const float4 *const q_hi = nodes + 2 * min(seg0 + max_moves, W - 2) + 2;
-    float g1 = ahead_of(*q, X, Y);
-    float g0;
-    bool fwd = false;
-    while (q < q_hi && g1 > 0.0f) {
-        q += 2;
-        g0 = g1;
-        g1 = ahead_of(*q, X, Y);
-        fwd = true;
+                                        int o0) {
+    const char *const base = (const char *)nodes;
+    auto row = [&](int o) { return *(const float4 *)(base + o); };  // geometry row at byte offset o = 32 node
+    const int hi = min(o0 + 32 * max_moves, 32 * (W - 2)) + 32;  // last row the forward walk may reach
+    int o = o0 + 32;                                            // row of node seg + 1
+    auto walk = [&](auto n_) {  // past the leading rows of o .. o + 32 (n - 1) that lie behind the point
+        constexpr int n = decltype(n_)::value;
+        float g[n];
+#pragma unroll
+        for (int j = 0; j < n; ++j) g[j] = ahead_of(row(o + 32 * j), X, Y);  // (past `hi`: inside LDS, not used)
+        int t = 32 * n;
+#pragma unroll
+        for (int j = n - 1; j >= 0; --j) t = g[j] > 0.0f ? t : 32 * j;
+        o = min(o + t, hi);
+        return t == 32 * n && o < hi;
+    };
+    if (o < hi) {
+        bool more = walk(std::integral_constant<int, 4>{});
+        while (more) more = walk(std::integral_constant<int, 2>{});
     }
-    seg = (int)(q - nodes) / 2 - 1;
-    q -= 2;  // geometry row of node seg
-    if (!fwd) g0 = ahead_of(*q, X, Y);
-    const float4 *const q_lo = nodes + 2 * max(0, seg - (max_moves - (seg - seg0)));
-    while (q > q_lo && g0 < 0.0f) {
-        q -= 2;
-        g1 = g0;
-        g0 = ahead_of(*q, X, Y);
+    o -= 32;  // row of the segment
+    float4 A0 = row(o), A1 = row(o + 32);
+    float g0 = ahead_of(A0, X, Y), g1 = ahead_of(A1, X, Y);
+    const int lo = max(0, 2 * o - o0 - 32 * max_moves);  // the moves left, backwards
+    if (__builtin_expect(o > lo && g0 < 0.0f, 0)) {
+        do {
+            o -= 32;
+            A1 = A0;
+            A0 = row(o);
+            g1 = g0;
+            g0 = ahead_of(A0, X, Y);
+        } while (o > lo && g0 < 0.0f);
     }
-    seg = (int)(q - nodes) / 2;
-    return foot_on(nodes, X, Y, seg, q[0], q[2], g0, g1);
+    return foot_on(nodes, X, Y, o, o, A0, A1, g0, g1);
 }
 
 // The same search with the geometry rows of segments seg .. seg + NPF - 1 read ahead
@@ -720,7 +784,7 @@ __device__ __forceinline__ Foot project_ahead(const float4 *__restrict__ nodes, 
         g1 = g0;
         g0 = ahead_of(nodes[2 * seg], X, Y);
     }
-    return foot_on(nodes, X, Y, seg, nodes[2 * seg], nodes[2 * seg + 2], g0, g1);
+    return foot_on(nodes, X, Y, 32 * seg, seg, nodes[2 * seg], nodes[2 * seg + 2], g0, g1);
 }
 
 // ------------------------------------------------------------------------------
@@ -791,9 +855,14 @@ __device__ __forceinline__ float wave_min_f32(float v) {
 // ------------------------------------------------------------------------------
 struct BlockState {
     int slot, race, agent, N, n_tail, n_opp, W, seg0, K, K_prop;
+    bool finite_u;  // the nominal, the proposal and the scales are finite (no NaN to keep in the clip)
     float vx0, vy0, om0, inv_n_tail, w_game;
     uint32_t key0, key1, ctr2, ctr3;
 };
+
+// Opponents screened together by the throughput variants (their far-away test is one compare
+// and one wave-wide branch for the group); groups of the lists' sizes 3, 9 and 15
+constexpr int OPP_GROUP = 3;
 
 template <int NDISC>
 __device__ void stage_block(const LaunchArgs &A, int item_idx, BlockState &bs, char *lds) {
@@ -907,8 +976,26 @@ __device__ void stage_block(const LaunchArgs &A, int item_idx, BlockState &bs, c
             const int j = jo < it.agent ? jo : jo + 1;
             footprint(t, jo, j, *(const float4 *)(A.pred_in + (size_t)(R.slot0 + j) * pstride + t * PRED_STRIDE));
         }
+        // centres far away for the opponents that fill the last group of OPP_GROUP up
+        const int pad = (bs.n_opp + OPP_GROUP - 1) / OPP_GROUP * OPP_GROUP - bs.n_opp;
+        if (pad > 0 && bs.n_opp + pad <= L.n_opp_max)
+            for (int e = tid; e < R.N * pad; e += nth) {
+                const int t = e / pad, jo = bs.n_opp + e - t * pad;
+                opp[((size_t)t * L.n_opp_max + jo) * (NDISC + 1)] = make_float2(1e15f, 1e15f);
+            }
     }
     __syncthreads();
+    bool bad = !isfinite(P.sigma_a) || !isfinite(P.sigma_d);
+    const int lane = tid & 63;
+    if (lane < bs.N) {  // (N <= 64: one row per lane, every wave for itself)
+        const float2 u = ubar[lane];
+        bad = bad || !isfinite(u.x) || !isfinite(u.y);
+        if (bs.K_prop > 0) {
+            const float4 q = ((const float4 *)(lds + L.prop))[lane];
+            bad = bad || !isfinite(q.x) || !isfinite(q.y) || !isfinite(q.z) || !isfinite(q.w);
+        }
+    }
+    bs.finite_u = __builtin_amdgcn_ballot_w64(bad) == 0;
 }
 
 // ------------------------------------------------------------------------------
@@ -916,19 +1003,21 @@ __device__ void stage_block(const LaunchArgs &A, int item_idx, BlockState &bs, c
 // functions on the same values and accumulate in the same order, so the
 // re-rolled sample reproduces its lane bit for bit.
 // ------------------------------------------------------------------------------
+template <bool CHECK = true>
 __device__ __forceinline__ float2 controls(const KParams &P, float2 ub, float za, float zd) {
-    return make_float2(clip_keep_nan(__builtin_fmaf(P.sigma_a, za, ub.x), P.a_min, P.a_max),
-                       clip_keep_nan(__builtin_fmaf(P.sigma_d, zd, ub.y), P.d_min, P.d_max));
+    return make_float2(clip_keep_nan<CHECK>(__builtin_fmaf(P.sigma_a, za, ub.x), P.a_min, P.a_max),
+                       clip_keep_nan<CHECK>(__builtin_fmaf(P.sigma_d, zd, ub.y), P.d_min, P.d_max));
 }
 // sample k < K_prop of a vehicle with a learned proposal: mean and scale from the proposal table
+template <bool CHECK = true>
 __device__ __forceinline__ float2 controls_k(const KParams &P, const BlockState &bs, const char *lds,
                                             const LdsLayout &L, uint32_t k, int tau, float2 ub, float za, float zd) {
-    if ((int)k < bs.K_prop) {
+    if (bs.K_prop > 0 && (int)k < bs.K_prop) {  // (the first test is wave-uniform)
         const float4 q = ((const float4 *)(lds + L.prop))[tau];
-        return make_float2(clip_keep_nan(__builtin_fmaf(q.z, za, q.x), P.a_min, P.a_max),
-                           clip_keep_nan(__builtin_fmaf(q.w, zd, q.y), P.d_min, P.d_max));
+        return make_float2(clip_keep_nan<CHECK>(__builtin_fmaf(q.z, za, q.x), P.a_min, P.a_max),
+                           clip_keep_nan<CHECK>(__builtin_fmaf(q.w, zd, q.y), P.d_min, P.d_max));
     }
-    return controls(P, ub, za, zd);
+    return controls<CHECK>(P, ub, za, zd);
 }
 
 // tracking term of eq. (ctrack) at one step; heading error wrapped to [-pi, pi]
@@ -1050,7 +1139,7 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
                                                    bool rear = false) {
     // parameters in single scalar registers, except in the one-lane latency variant
     // (about one wave per SIMD), which measured faster with the compiler's own allocation
-    const KParams P = (NPF > 0 && LPS == 1) ? P_in : loop_params(P_in);
+    KParams P = (NPF > 0 && LPS == 1) ? P_in : loop_params(P_in);
     const float2 *ubar = (const float2 *)(lds + L.ubar);
     const float4 *xref = (const float4 *)(lds + L.xref);
     const float2 *opp = (const float2 *)(lds + L.opp);
@@ -1060,10 +1149,20 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
     if constexpr (NPF == 0 && LPS == 1) {  // throughput variants: the dynamics' hot constants
         V.B = vreg(V.B); V.Cs = vreg(V.Cs); V.lf = vreg(V.lf); V.lr = vreg(V.lr);
         V.kr_m = vreg(V.kr_m); V.kr_Iz = vreg(V.kr_Iz); h = vreg(h);
+        // (a median takes one scalar operand; with more opponents these two would spill)
+        if constexpr (MAXOPP <= 3) { P.a_max = vreg(P.a_max); P.d_max = vreg(P.d_max); }
     }
 
+    // throughput variants: four waves per SIMD, bound by VALU issue (94 % of the issue cycles
+    // used), so what counts is the number of instructions, above all of those that are never
+    // issued in pairs (integer, compare, select, scalar operands).  The Philox products and
+    // box clips that a step does not need, the short Box-Muller division and root, the
+    // scalar step number, the batched raceline walk and the opponents' groups together took
+    // the 256-race batch from 128.7 to 122.3 ms per planning step, the large field from 3.50
+    // to 3.36 ms and 32 races with the learned proposal from 2.71 to 2.59 ms, same bits.
+    constexpr bool THR = NPF == 0 && LPS == 1;
     float st[6] = {0.0f, 0.0f, 0.0f, bs.vx0, bs.vy0, bs.om0};
-    int seg = bs.seg0;
+    int seg = NPF == 0 ? 32 * bs.seg0 : bs.seg0;  // (project's byte offset)
     float J = 0.0f, rho_bd = INFINITY, dsum = 0.0f, s = 0.0f;
     float g2[MAXOPP];
 #pragma unroll
@@ -1079,19 +1178,23 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
     const int C = (bs.N + NC - 1) / NC;
 
     float2 zn = make_float2(0.0f, 0.0f);  // perturbation of the odd step of a Philox call
+    const PhiloxLane pl = philox_lane(k, bs.ctr2, bs.ctr3, bs.key0, bs.key1);
     // throughput variants: the heading's cosine and sine after a step (the footprint's) are
     // the first RK4 stage's of the next step, computed once
-    constexpr bool HCS = NPF == 0 && LPS == 1;
+    constexpr bool HCS = THR;
     float hc = 0.0f, hs = 0.0f;
     if constexpr (HCS) {
         hc = fast_cos(st[2]);
         hs = fast_sin(st[2]);
     }
-    for (int tau = 0; tau < bs.N; ++tau) {
+    for (int next = 0; next < bs.N;) {
+        // the step number stays in a scalar register (left alone, the compiler holds it in a
+        // vector register and forms every address and test of the step from it there)
+        const int tau = __builtin_amdgcn_readfirstlane(next);
+        next = tau + 1;
         float2 z;
         if ((tau & 1) == 0) {
-            const uint4 r = philox4x32_10<NPF == 0 && LPS == 1>(make_uint4(k, (uint32_t)(tau >> 1), bs.ctr2, bs.ctr3),
-                                                                bs.key0, bs.key1);
+            const uint4 r = philox_call<THR>(pl, (uint32_t)(tau >> 1), bs.key0, bs.key1);
             if constexpr (LPS == 2) {
                 const float2 g = gauss_pair(rear ? r.z : r.x, rear ? r.w : r.y);
                 const float2 go = make_float2(dpp_swap_f32(g.x), dpp_swap_f32(g.y));
@@ -1121,7 +1224,9 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
             noise_out[2 * tau] = z.x;
             noise_out[2 * tau + 1] = z.y;
         }
-        const float2 u = controls_k(P, bs, lds, L, k, tau, ub, z.x, z.y);
+        float2 u;
+        if (THR && __builtin_expect(bs.finite_u, 1)) u = controls_k<false>(P, bs, lds, L, k, tau, ub, z.x, z.y);
+        else u = controls_k(P, bs, lds, L, k, tau, ub, z.x, z.y);
         // latency variants (NPF > 0) branch-free, throughput variants with the uniform atan
         using MS = typename std::conditional<NPF == 0, MathF32U, MathF32>::type;
         const StepConst<float> sc = step_const<MODEL, MS>(V, u.x, u.y);
@@ -1139,6 +1244,10 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
         if (tau >= 1) J += rate_term(P, u, up);
         up = u;
         rho_bd = fminf(rho_bd, bound_term(f));
+        if (tau + 1 > bs.N - bs.n_tail) dsum += f.d;
+        // the foot is finished here: left to the compiler it moves past the opponents, whose
+        // rare path then spills the rows it holds
+        if constexpr (THR) asm volatile("" : "+v"(rho_bd), "+v"(dsum), "+v"(s));
         float ch = 1.0f, sh = 0.0f;
         if constexpr (HCS) {
             hc = fast_cos(st[2]);
@@ -1149,34 +1258,46 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
             ch = fast_cos(st[2]);
             sh = fast_sin(st[2]);
         }
-        // (other variants with up to 3 opponents read every centre before the first test,
-        // all within the table; more would hold too many registers)
-        constexpr int NPRE = (!PRE_ALL && MAXOPP <= 3) ? MAXOPP : 1;
-        float2 cg[NPRE];
-        if constexpr (!PRE_ALL && MAXOPP <= 3) {
-#pragma unroll
-            for (int j = 0; j < NPRE; ++j) cg[j] = ot[j * (NDISC + 1)];
-        }
-        float ax[NDISC], ay[NDISC];
-        disc_centres<NDISC>(P, st[0], st[1], ch, sh, ax, ay);
         // opponent count compared on the scalar unit at every step (held as one compare mask
         // per opponent, the masks were spilled and reloaded with v_readlane)
         int n_opp = bs.n_opp;
         asm volatile("" : "+s"(n_opp));
+        float ax[NDISC], ay[NDISC];
+        if constexpr (THR) {
+            // the centres of a group are read together and the nearest one decides for all of
+            // them; a group no lane is close to (the common case) costs one compare and branch
+            constexpr int NG = MAXOPP < OPP_GROUP ? MAXOPP : OPP_GROUP;
 #pragma unroll
-        for (int j = 0; j < MAXOPP; ++j) {
-            if (j < n_opp) {
-                if constexpr (PRE_ALL) {
-                    g2[j] = opp_min2<NDISC>(P, orow + j * (NDISC + 1), orow[j * (NDISC + 1)], st[0], st[1], ax, ay,
-                                            g2[j]);
-                } else {
-                    const float2 c0 = MAXOPP <= 3 ? cg[j < NPRE ? j : 0] : ot[j * (NDISC + 1)];
-                    g2[j] = opp_min2<NDISC, NPF == 0 && LPS == 1>(P, ot + j * (NDISC + 1), c0, st[0], st[1], ax,
-                                                                  ay, g2[j]);
+            for (int j0 = 0; j0 < MAXOPP; j0 += NG) {
+                if (j0 >= n_opp) break;
+                float d2 = 0.0f;
+#pragma unroll
+                for (int j = 0; j < NG; ++j) {
+                    const float2 c0 = ot[(j0 + j) * (NDISC + 1)];
+                    const float dx = st[0] - c0.x, dy = st[1] - c0.y;
+                    const float e2 = dx * dx + dy * dy;
+                    d2 = j == 0 ? e2 : fminf(d2, e2);
+                }
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(d2 < P.skip2) == 0, 1)) continue;
+                float c = ch, d = sh;  // (opaque: the own disc centres are formed in this branch only)
+                asm volatile("" : "+v"(c), "+v"(d));
+                disc_centres<NDISC>(P, st[0], st[1], c, d, ax, ay);
+#pragma unroll
+                for (int j = j0; j < j0 + NG; ++j)
+                    if (j < n_opp)
+                        g2[j] = opp_min2<NDISC, true>(P, ot + j * (NDISC + 1), ot[j * (NDISC + 1)], st[0], st[1], ax, ay,
+                                                      g2[j]);
+            }
+        } else {
+            disc_centres<NDISC>(P, st[0], st[1], ch, sh, ax, ay);
+#pragma unroll
+            for (int j = 0; j < MAXOPP; ++j) {
+                if (j < n_opp) {
+                    const float2 *e = PRE_ALL ? orow + j * (NDISC + 1) : ot + j * (NDISC + 1);
+                    g2[j] = opp_min2<NDISC>(P, e, e[0], st[0], st[1], ax, ay, g2[j]);
                 }
             }
         }
-        if (tau + 1 > bs.N - bs.n_tail) dsum += f.d;
         // (C re-read at every step: the step counts (c + 1) C are not kept in registers)
         int Cv = C;
         asm volatile("" : "+s"(Cv));
@@ -1486,7 +1607,7 @@ __device__ void reroll_block(const KParams &P, const LdsLayout &L, const BlockSt
     const int pch = tid - 64;
     volatile int *prog = (volatile int *)(lds + L.rr_sync);
     float st[6] = {0.0f, 0.0f, 0.0f, bs.vx0, bs.vy0, bs.om0};
-    int seg = bs.seg0;
+    int seg = NPF == 0 ? 32 * bs.seg0 : bs.seg0;  // (as the sample's lane counts it)
     if (chunk_lane && ch > 0) {
         const float *c = cps + 7 * (ch - 1);
 #pragma unroll
