@@ -138,7 +138,7 @@ int sgtp_ctx_create(sgtp_ctx **out, int max_agents_total, int max_N, int max_rac
                     int max_K);
 int sgtp_ctx_destroy(sgtp_ctx *ctx);
 const char *sgtp_last_error(const sgtp_ctx *ctx);
-/* The two-wave sweep variant (and the winner re-roll) pass states and controls between
+/* The four-wave sweep variant (and the winner re-roll) pass states and controls between
  * waves of a workgroup through LDS and wait for each other with bounded polls.  Both
  * waits always end by construction; should one give up all the same, the kernel scores
  * that sample non-finite (so it is never selected) and raises a bit of the context's
@@ -226,12 +226,14 @@ int sgtp_advance(sgtp_ctx *ctx, const sgtp_params *p, const sgtp_race *races, in
  * output arrays, uploads their descriptors once and runs Alg. 1 for all races per
  * call: one setup launch, then one sweep launch per phase covering every vehicle
  * of every race.  Tiles of BLOCK = 256 samples (x samples_per_lane) are the unit
- * of work; small plans (at most 65536 samples over all vehicles, at most 3
- * opponents, one sample per lane) run 128-sample tiles with each sample on two waves
- * (dynamics on one; perturbation, projection and scoring on the other), or, where
- * those LDS rings do not fit, with each sample on a pair of lanes (dynamic model,
- * feasibility selection, at most 32768 samples); these plans run one workgroup per
- * tile (persistent is ignored).  Every variant gives the same per-sample bits.  A
+ * of work; a sweep over at most 65536 samples (49152 with more than 3 opponents; one
+ * sample per lane) runs 64-sample tiles whose work is dealt out to the four waves of
+ * a workgroup (dynamics on two; perturbation and cost terms; projection, opponents
+ * and scoring), or, where those LDS rings do not fit, with each sample on a pair of
+ * lanes (dynamic model, feasibility selection, at most 32768 samples and 3
+ * opponents); such sweeps run one workgroup per tile (persistent is ignored; the
+ * extra ego response takes this form by its own sample count).  Every variant gives
+ * the same per-sample bits.  A
  * persistent sweep keeps a fixed grid of workgroups that pull chunks of
  * tiles from 8 queues (vehicles assigned longest-first; a workgroup serves its own
  * queue first, then steals), re-staging LDS only when the vehicle changes.  With

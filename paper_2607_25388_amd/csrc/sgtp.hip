@@ -44,21 +44,25 @@ constexpr int PRED_STRIDE = 8;  // x, y, cos psi, sin psi, s_rel, d, -, - in the
 constexpr int NODE_STRIDE = 10; // device node row: x, y, psi, nx, ny, wL, wR, vref, s, kappa
 constexpr unsigned long long KEY_NONE = ~0ull;
 constexpr long long LPS2_MAX_SAMPLES = 32768;  // pair variant up to 1024 waves
-// Split variant (launches of about one wave per SIMD or fewer): each sample runs on two
-// waves, dynamics on one and projection and scoring on the other, its states passing
-// through an LDS ring of SPLIT_RING steps.
-constexpr long long SPLIT_MAX_SAMPLES = 65536;  // up to 2048 waves
-constexpr int SPLIT_RING = 4;
-constexpr int SPLIT_AHEAD = 2;  // controls published ahead of the state being scored (2 and a
-                                // ring of 4 measured faster than 1, 3, 4 or 6 and a ring of 8)
-constexpr int SPLIT_FIN = 8;    // floats per sample handed from the dynamics to the scoring lane
-// The split variant's roles by wave: even waves integrate the dynamics, odd waves score,
-// wave 2j + 1 partnering wave 2j.  A workgroup's four waves occupy the CU's four SIMDs in
-// a fixed cyclic order, and the next workgroup resident on the same CU starts one SIMD
-// further along it (measured); with the roles in halves, two resident workgroups put two
-// dynamics chains on one SIMD, with alternating roles every SIMD holds one chain and one
-// scoring wave.  Virtual thread index: role x 128 + wave pair x 64 + lane.
-__device__ __forceinline__ int split_vt(int t) { return ((t >> 6) & 1) * (BLOCK / 2) + ((t >> 7) << 6) + (t & 63); }
+// Team variant (launches too small to fill the chip with one lane per sample): 64 samples on
+// the four waves of a workgroup, each wave with a part of the work of every step (see
+// lane_sample_team).
+constexpr long long TEAM_MAX_SAMPLES = 65536, TEAM_MAX_SAMPLES_WIDE = 49152;
+constexpr int TEAM = 64;         // samples per workgroup
+constexpr int TEAM_RING = 4;     // steps in the rings of controls and of states
+constexpr int TEAM_AHEAD = 2;    // controls published ahead of the state being scored
+constexpr int TEAM_CTRL = 2, TEAM_SCORE = 3;  // the wave that draws a sample's controls, the one that scores it
+// words of the team's LDS counters: controls written, states written (by up to two waves),
+// states read (controls' wave, scoring wave, opponents' wave)
+// rows of its values handed over at the end: final state, cost sum, squared clearances
+enum { TF_ST = 0, TF_J = 6, TF_G2 = 7 };
+enum { TS_U = 0, TS_S = 2, TS_READ = 4, TS_BEST = 7, TS_STALL = 8, TS_WORDS = 12 };
+// The sample of the team a thread works on.  The dynamic model's states are integrated by two
+// waves, 32 samples each on a pair of lanes (one axle per lane).
+template <int MODEL>
+__device__ __forceinline__ int team_sample(int t) {
+    return MODEL == 0 && t < 128 ? t >> 1 : t & 63;
+}
 constexpr int NQ = 8;           // tile queues of the persistent sweep (one per XCD under round-robin dispatch)
 // Re-roll chunks: each lane keeps its state after every ceil(N / chunks) steps, so the
 // selected sample is re-rolled in that many pieces at once.  Latency variants (about
@@ -92,7 +96,7 @@ struct KParams {
     float g_safe, m_bd, d_col;
     float inv_lambda, w_viol;                                // path-integral update
     float pred_sig_lon, pred_sig_lat;                        // opponent-prediction perturbation
-    int spin_limit;  // polls of a bounded LDS wait (split variant, winner re-roll) before it gives up
+    int spin_limit;  // polls of a bounded LDS wait (team variant, winner re-roll) before it gives up
 };
 
 struct TrackDev {
@@ -131,9 +135,10 @@ struct LdsLayout {  // byte offsets of the staged tables, identical for every bl
     int ubar, xref, oppT, oppc, opp, nodes, prop;
     int rr_u, rr_st, rr_f, rr_t;  // re-roll scratch (rr_t: setup's reference recursion)
     int rr_sync;                  // re-roll: states written per piece (NCP_MAX ints)
-    int sp_ring, sp_uring, sp_sync, sp_fin;  // split variant: state and control rings, counters, final state
-    int total;
+    int sp_uring, sp_sring, sp_sync, sp_fin;  // team variant: rings, counters, values handed over at the end
+    int total, total_team;  // bytes of a launch without / with the team variant's part
     int n_opp_max, w_max, N_max;
+    int w_stage;  // window rows a sweep stages (k_setup: w_max)
 };
 
 struct LaunchArgs {
@@ -144,7 +149,8 @@ struct LaunchArgs {
     const ItemDev *items;
     int n_items, n_tiles, spl, phase;
     int lps;               // lanes per sample (2: the pair variant of small launches)
-    int split;             // 1: the split variant (two waves per sample)
+    int team;              // 1: the team variant (four waves for 64 samples)
+    int pi_teams;          // path integral: teams per partial sum (2 or 4)
     AgentRec *agents;
     const float4 *win;     // [slot][WIN_MAX][2]
     const float4 *xref;    // [slot][N_max]
@@ -431,6 +437,11 @@ struct MathF32U : MathF32 {
     static __device__ __forceinline__ T atan_slip_(T x) { return atan_slip<true>(x); }
 };
 
+// MathF32 with the wave-uniform test of the slip angles only (integrating waves of a team)
+struct MathF32S : MathF32 {
+    static __device__ __forceinline__ T atan_slip_(T x) { return atan_slip<true>(x); }
+};
+
 struct MathF64 {
     using T = double;
     static __device__ __forceinline__ T atan_(T x) { return ::atan(x); }
@@ -546,23 +557,27 @@ __device__ __forceinline__ void deriv(const VehConst<typename M::T> &V, const St
     deriv_cs<MODEL, M>(V, c, M::cos_rev(pr), M::sin_rev(pr), vx_, vy, om, d);
 }
 
-// Value of the neighbouring lane of a pair (quad permute [1, 0, 3, 2]).
-__device__ __forceinline__ float dpp_swap_f32(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, false));
+// Quad permutes; 0xB1: the neighbouring lane of a pair ([1, 0, 3, 2]), 0xA0 / 0xF5: the even /
+// odd lane of the pair ([0, 0, 2, 2], [1, 1, 3, 3]).
+template <int CTRL>
+__device__ __forceinline__ float dpp_quad_f32(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
+__device__ __forceinline__ float dpp_swap_f32(float v) { return dpp_quad_f32<0xB1>(v); }
 
 // The dynamic model's derivative on a pair of neighbouring lanes: each lane evaluates
-// one axle (rear = odd lane) and the two forces are swapped with a DPP quad permute;
+// one axle (rear = odd lane) and the two forces are exchanged by DPP quad permutes;
 // everything else is computed by both lanes alike.  Same values as deriv<0, MathF32>.
+template <class M = MathF32>
 __device__ __forceinline__ void deriv_pair(const VehConst<float> &V, const StepConst<float> &c, float psi, float vx_,
                                            float vy, float om, bool rear, float d[6]) {
     const float vx = MathF32::pos_(vx_);
     const float pr = MathF32::to_rev(psi);
     const float cp = MathF32::cos_rev(pr), sp = MathF32::sin_rev(pr);
     const float inv_vh = MathF32::rcp_(MathF32::pos_floor_(vx_, V.v_eps));
-    const float F = tyre_force<MathF32>(V, rear ? -V.lr : V.lf, rear ? 0.0f : c.delta, vy, om, inv_vh);
-    const float Fo = dpp_swap_f32(F);
-    deriv_rates<MathF32>(V, c, vx, vy, om, cp, sp, rear ? Fo : F, rear ? F : Fo, d);
+    const float F = tyre_force<M>(V, rear ? -V.lr : V.lf, rear ? 0.0f : c.delta, vy, om, inv_vh);
+    // the front force from the even lane of the pair, the rear one from the odd lane
+    deriv_rates<MathF32>(V, c, vx, vy, om, cp, sp, dpp_quad_f32<0xA0>(F), dpp_quad_f32<0xF5>(F), d);
 }
 
 // Classic RK4 over one interval with the control held, then v_x <- max(v_x, 0).
@@ -587,14 +602,15 @@ __device__ __forceinline__ void rk4(const VehConst<typename M::T> &V, const Step
 }
 
 // rk4<0, MathF32> on a pair of lanes (deriv_pair); same expressions, same bits.
+template <class M = MathF32>
 __device__ __forceinline__ void rk4_pair(const VehConst<float> &V, const StepConst<float> &c, float h, float s[6],
                                          bool rear) {
     float k1[6], k2[6], k3[6], k4[6];
     const float hh = 0.5f * h;
-    deriv_pair(V, c, s[2], s[3], s[4], s[5], rear, k1);
-    deriv_pair(V, c, s[2] + hh * k1[2], s[3] + hh * k1[3], s[4] + hh * k1[4], s[5] + hh * k1[5], rear, k2);
-    deriv_pair(V, c, s[2] + hh * k2[2], s[3] + hh * k2[3], s[4] + hh * k2[4], s[5] + hh * k2[5], rear, k3);
-    deriv_pair(V, c, s[2] + h * k3[2], s[3] + h * k3[3], s[4] + h * k3[4], s[5] + h * k3[5], rear, k4);
+    deriv_pair<M>(V, c, s[2], s[3], s[4], s[5], rear, k1);
+    deriv_pair<M>(V, c, s[2] + hh * k1[2], s[3] + hh * k1[3], s[4] + hh * k1[4], s[5] + hh * k1[5], rear, k2);
+    deriv_pair<M>(V, c, s[2] + hh * k2[2], s[3] + hh * k2[3], s[4] + hh * k2[4], s[5] + hh * k2[5], rear, k3);
+    deriv_pair<M>(V, c, s[2] + h * k3[2], s[3] + h * k3[3], s[4] + h * k3[4], s[5] + h * k3[5], rear, k4);
     const float h6 = h / 6.0f;
 #pragma unroll
     for (int i = 0; i < 6; ++i) s[i] = s[i] + h6 * (k1[i] + 2.0f * k2[i] + 2.0f * k3[i] + k4[i]);
@@ -742,8 +758,9 @@ __device__ __forceinline__ Foot project(const float4 *__restrict__ nodes, int W,
 }
 
 // The same search with the geometry rows of segments seg .. seg + NPF - 1 read ahead
-// (before the step's dynamics, so their LDS latency is hidden): the first NPF - 2
-// forward moves are decided on registers, further moves read LDS.  Same result.
+// (before the step's dynamics, so their LDS latency is hidden): the first NPF - 1
+// forward moves are decided on registers, further moves read LDS, NPF - 1 rows at a time.
+// Same result.
 template <int NPF>
 struct NodeAhead {
     float4 q[NPF];
@@ -758,33 +775,35 @@ __device__ __forceinline__ NodeAhead<NPF> read_ahead(const float4 *__restrict__ 
 template <int NPF>
 __device__ __forceinline__ Foot project_ahead(const float4 *__restrict__ nodes, int W, int max_moves, float X,
                                               float Y, int seg, const NodeAhead<NPF> &a) {
+    const int last = min(seg + max_moves, W - 2);  // last segment the forward walk may reach
     float g[NPF];
 #pragma unroll
     for (int i = 0; i < NPF; ++i) g[i] = ahead_of(a.q[i], X, Y);
-    int moves = 0;
-    float g0 = g[0], g1 = g[1];
-    bool go = true;
+    // leading rows seg + 1, ... that lie behind the point
+    int t = NPF - 1;
 #pragma unroll
-    for (int i = 1; i < NPF - 1; ++i) {
-        go = go && moves < max_moves && seg + 1 <= W - 2 && g1 > 0.0f;
-        seg += go ? 1 : 0;
-        moves += go ? 1 : 0;
-        g0 = go ? g1 : g0;
-        g1 = go ? g[i + 1] : g1;
+    for (int i = NPF - 1; i >= 1; --i) t = g[i] > 0.0f ? t : i - 1;
+    const int seg0 = seg;
+    seg = min(seg + t, last);
+    if (__builtin_expect(t == NPF - 1, 0)) {
+        while (seg < last && t == NPF - 1) {  // beyond the rows at hand: more of them, read together
+            float h[NPF - 1];
+#pragma unroll
+            for (int i = 0; i < NPF - 1; ++i) h[i] = ahead_of(nodes[2 * min(seg + 1 + i, W - 1)], X, Y);
+#pragma unroll
+            for (int i = NPF - 2; i >= 0; --i) t = h[i] > 0.0f ? t : i;
+            seg = min(seg + t, last);
+        }
     }
-    while (go && moves < max_moves && seg + 1 <= W - 2 && g1 > 0.0f) {
-        ++seg;
-        ++moves;
-        g0 = g1;
-        g1 = ahead_of(nodes[2 * seg + 2], X, Y);
+    if (__builtin_expect(t == 0 && g[0] < 0.0f, 0)) {  // (no move forward: the whole budget is left)
+        float g0 = g[0];
+        for (int moves = seg - seg0; moves < max_moves && seg > 0 && g0 < 0.0f; ++moves) {
+            --seg;
+            g0 = ahead_of(nodes[2 * seg], X, Y);
+        }
     }
-    while (moves < max_moves && seg > 0 && g0 < 0.0f) {
-        --seg;
-        ++moves;
-        g1 = g0;
-        g0 = ahead_of(nodes[2 * seg], X, Y);
-    }
-    return foot_on(nodes, X, Y, 32 * seg, seg, nodes[2 * seg], nodes[2 * seg + 2], g0, g1);
+    const float4 A0 = nodes[2 * seg], A1 = nodes[2 * seg + 2];
+    return foot_on(nodes, X, Y, 32 * seg, seg, A0, A1, ahead_of(A0, X, Y), ahead_of(A1, X, Y));
 }
 
 // ------------------------------------------------------------------------------
@@ -896,10 +915,10 @@ __device__ void stage_block(const LaunchArgs &A, int item_idx, BlockState &bs, c
     float2 *ubar = (float2 *)(lds + L.ubar);
     float4 *xref = (float4 *)(lds + L.xref);
     float4 *nodes = (float4 *)(lds + L.nodes);
-    // window and reference rows: whole buffers (w_max, N_max rows), so these reads do not
+    // window and reference rows: whole buffers (w_stage, N_max rows), so these reads do not
     // wait for the vehicle record; rows past the vehicle's own are never read
     const float4 *wn = A.win + (size_t)it.slot * WIN_MAX * 2;
-    for (int t = tid; t < 2 * L.w_max; t += nth) nodes[t] = wn[t];
+    for (int t = tid; t < 2 * L.w_stage; t += nth) nodes[t] = wn[t];
     const float4 *xr = A.xref + (size_t)it.slot * L.N_max;
     for (int t = tid; t < L.N_max; t += nth) xref[t] = xr[t];
     const float2 *un = (const float2 *)(R.u_nom) + (size_t)it.agent * R.N;
@@ -1319,249 +1338,280 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
 }
 
 // ------------------------------------------------------------------------------
-// One sample on two waves (the split variant).  A lane of an even wave integrates the
-// dynamics, the longest dependent chain of a step.  Its partner lane in the next (odd)
-// wave does the rest: it draws the perturbation and clips the controls
-// SPLIT_AHEAD steps ahead, projects every state onto the raceline and scores it
-// (tracking, control and rate terms, boundary, footprint distances, tail offsets), then
-// takes the terminal scoring.  Controls and states pass through LDS rings of SPLIT_RING
-// steps; uprod / prod count the controls and states written, cons the states consumed,
-// per wave pair, and each side re-reads a count only when its ring runs empty (or full).
-// The scoring side publishes the controls of step tau + SPLIT_AHEAD before it waits for
-// state tau, and a control slot is rewritten only after its state was published, so
-// both waits end; their bounds are guards only (a wait polls every 256 cycles: shorter
-// sleeps took issue slots from the wave sharing the SIMD, longer ones woke late).  Checkpoints: states on the dynamics
-// lane, segments on the scoring lane.  Arithmetic and summation order as in lane_sample:
-// the two variants give the same bits.
+// 64 samples on the four waves of a workgroup (the team variant of small launches).  Alone on
+// its SIMD a wave issues at most one instruction every eight clocks whatever it is, so the
+// time of a step is the longest instruction stream that one wave carries; the step's work is
+// dealt out so that the waves carry about the same (200 to 250 instructions; one lane per
+// sample: 640):
+//   dynamic model: waves 0 and 1 integrate the states of 32 samples each, a pair of lanes per
+//     sample (one axle per lane); kinematic bicycle: wave 0 integrates all 64 states, wave 1
+//     takes the distances to the opponents;
+//   wave 2 draws the perturbations, clips the controls TEAM_AHEAD steps ahead and sums the
+//     tracking, control and rate terms;
+//   wave 3 projects the states onto the raceline, takes the opponents' distances (dynamic
+//     model) and the terminal scoring.
+// Controls and states pass through LDS rings of TEAM_RING steps, whose counters are each
+// written by one lane after the slot and polled by the readers.  No wait depends on itself:
+// wave 2 publishes the controls of step tau + TEAM_AHEAD before it waits for state tau; an
+// integrating wave waits for the control of its step and for a free slot, that is for states
+// published TEAM_RING steps ago to be read; the readers wait only for states.  The polls are
+// bounded all the same (P.spin_limit): a team whose wait gave up is scored non-finite.
+// Arithmetic and summation order are those of lane_sample: the same bits.
+//   One planning step against two waves per 64 samples (dynamics | everything else): see the
+// dispatch rule (team_list).  Measured and not kept: position and heading integrated by the
+// scoring wave from the stages' velocities (shorter streams, but one more hand-over per step:
+// mid-scale race +3 %).
 // ------------------------------------------------------------------------------
+// The LDS accesses of one wave are carried out in the order in which it issues them, so a
+// counter written after its slot is seen after the slot, and a slot read before its counter
+// is written was read before: between waves of a workgroup that exchange through LDS alone
+// the compiler's order is all that is needed (a workgroup fence would also wait for every
+// access in flight, at each counter).
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
 template <int MODEL, int NDISC, int MAXOPP, int NPF>
-__device__ __forceinline__ SampleResult lane_sample_split(const KParams &P, const BlockState &bs, char *lds,
-                                                         const LdsLayout &L, uint32_t k, float *noise_out, bool dyn,
-                                                         int *status) {
-    constexpr int TS = BLOCK / 2;
+__device__ __forceinline__ SampleResult lane_sample_team(const KParams &P, const BlockState &bs, char *lds,
+                                                        const LdsLayout &L, uint32_t k, float *noise_out,
+                                                        int *status) {
     constexpr int NC = ncp_of<NPF>();
-    static_assert(SPLIT_AHEAD + 1 <= SPLIT_RING, "a control slot is rewritten only after its state was published");
-    const int vt = split_vt(threadIdx.x);
-    const int i = vt & (TS - 1);
-    const int w = (vt >> 6) & 1;  // wave pair
+    constexpr int ND = MODEL == 0 ? 2 : 1;  // integrating waves
+    constexpr bool OPP_WAVE = MODEL != 0;   // wave 1 takes the opponents
+    static_assert(TEAM_AHEAD + 1 <= TEAM_RING, "a control slot is rewritten only after its state was published");
+    static_assert(TEAM_AHEAD == 2, "the controls between publication and scoring are held in two registers");
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    float4 *ring = (float4 *)(lds + L.sp_ring);    // [SPLIT_RING][TS]: X, Y, PSI, VX after the step
-    float2 *uring = (float2 *)(lds + L.sp_uring);  // [SPLIT_RING][TS]: controls of the step
-    volatile int *prod = (volatile int *)(lds + L.sp_sync);
-    volatile int *cons = prod + 2;
-    volatile int *uprod = prod + 6;
-    float *fin = (float *)(lds + L.sp_fin);  // [TS][SPLIT_FIN]: final state
-    const int C = (bs.N + NC - 1) / NC;
-    if (threadIdx.x < 8) prod[threadIdx.x] = 0;
+    const int i = team_sample<MODEL>(threadIdx.x);
+    float2 *uring = (float2 *)(lds + L.sp_uring);  // [TEAM_RING][TEAM]: controls of the step
+    float4 *sring = (float4 *)(lds + L.sp_sring);  // [TEAM_RING][TEAM]: X, Y, PSI, VX after the step
+    volatile int *sync = (volatile int *)(lds + L.sp_sync);
+    float *fin = (float *)(lds + L.sp_fin);        // [TF_* rows][TEAM]
+    const int N = bs.N;
+    if (threadIdx.x < TS_WORDS) sync[threadIdx.x] = 0;
     __syncthreads();
-    // each side's values, set and used only on that side (one barrier, outside both)
-    float cp[NC - 1][6];                                   // dynamics: checkpointed states
-    float J, rho_bd, dsum, s, g2[MAXOPP];                  // scoring
-    bool limit;
-    int cseg[NC - 1];
-    // a wait that gave up (its partner did not advance within P.spin_limit polls): the
-    // sample's values are then unreliable, so it is scored non-finite (never selected)
     bool stalled = false;
-    if (dyn) {
-        const VehConst<float> V = veh_f32(P);
-        float st[6] = {0.0f, 0.0f, 0.0f, bs.vx0, bs.vy0, bs.om0};
+    // wait until `count()` exceeds tau (the last value read is kept in `seen`)
+    auto wait_for = [&](int tau, int &seen, auto count) {
+        if (seen > tau) return;
+        for (int spin = 0; spin < P.spin_limit; ++spin) {
+            seen = __builtin_amdgcn_readfirstlane(count());
+            if (seen > tau) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        stalled |= seen <= tau;
+        lds_order();
+    };
+    auto publish = [&](int j, int v) {
+        lds_order();
+        if (lane == 0) sync[j] = v;
+    };
+    auto states = [&]() {
+        const int a = sync[TS_S];
+        return ND == 2 ? min(a, (int)sync[TS_S + 1]) : a;
+    };
+    // squared distances to the opponents
+    const float2 *opp = (const float2 *)(lds + L.opp);
+    constexpr bool PRE = MAXOPP <= 3;  // the step's rows read ahead of the state (registers allow)
+    constexpr int OROW = PRE ? MAXOPP * (NDISC + 1) : 1;
+    float g2[MAXOPP];
 #pragma unroll
-        for (int c = 0; c < NC - 1; ++c)
+    for (int j = 0; j < MAXOPP; ++j) g2[j] = P.cap2;
+    auto opp_rows = [&](int tau, float2 *orow) {
+        if constexpr (PRE) {
+            const float2 *ot = opp + tau * (L.n_opp_max * (NDISC + 1));
 #pragma unroll
-            for (int j = 0; j < 6; ++j) cp[c][j] = 0.0f;
-        int useen = 0, seen = 0;  // the scoring side's counts as last read
-        for (int tau = 0; tau < bs.N; ++tau) {
-            if (useen <= tau) {
-                for (int spin = 0; spin < P.spin_limit; ++spin) {
-                    useen = uprod[w];
-                    if (useen > tau) break;
-                    __builtin_amdgcn_s_sleep(4);
-                }
-                stalled |= useen <= tau;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            }
-            const float2 u = uring[(tau % SPLIT_RING) * TS + i];
-            const StepConst<float> sc = step_const<MODEL, MathF32>(V, u.x, u.y);
-            rk4<MODEL, MathF32>(V, sc, P.dt, st);
-            if (tau - seen >= SPLIT_RING) {
-                for (int spin = 0; spin < P.spin_limit; ++spin) {
-                    seen = cons[w];
-                    if (tau - seen < SPLIT_RING) break;
-                    __builtin_amdgcn_s_sleep(4);
-                }
-                stalled |= tau - seen >= SPLIT_RING;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            }
-            ring[(tau % SPLIT_RING) * TS + i] = make_float4(st[0], st[1], st[2], st[3]);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (lane == 0) prod[w] = tau + 1;
-            int Cv = C;
-            asm volatile("" : "+s"(Cv));
+            for (int j = 0; j < OROW; ++j) orow[j] = ot[j];
+        }
+    };
+    auto opponents = [&](int tau, const float2 *orow, float4 sv) {
+        const float2 *ot = opp + tau * (L.n_opp_max * (NDISC + 1));
+        float ch = 1.0f, sh = 0.0f;
+        if (NDISC > 1) {
+            ch = fast_cos(sv.z);
+            sh = fast_sin(sv.z);
+        }
+        float ax[NDISC], ay[NDISC];
+        disc_centres<NDISC>(P, sv.x, sv.y, ch, sh, ax, ay);
+        int n_opp = bs.n_opp;
+        asm volatile("" : "+s"(n_opp));
 #pragma unroll
-            for (int c = 0; c < NC - 1; ++c) {
-                if (tau + 1 == (c + 1) * Cv) {
-#pragma unroll
-                    for (int j = 0; j < 6; ++j) cp[c][j] = st[j];
-                }
+        for (int j = 0; j < MAXOPP; ++j) {
+            if (j < n_opp) {
+                const float2 *e = PRE ? orow + j * (NDISC + 1) : ot + j * (NDISC + 1);
+                g2[j] = opp_min2<NDISC, !PRE>(P, e, e[0], sv.x, sv.y, ax, ay, g2[j]);
             }
         }
+    };
+    // checkpoints after steps C, 2 C, ...: one comparison per step, the number only then;
+    // states on the integrating waves, segments (in the first place) on the scoring wave
+    float cp[NC - 1][6];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) fin[i * SPLIT_FIN + j] = st[j];
-        fin[i * SPLIT_FIN + 6] = stalled ? 1.0f : 0.0f;
-    } else {
+    for (int c = 0; c < NC - 1; ++c)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) cp[c][j] = 0.0f;
+    const int C = (N + NC - 1) / NC;
+    int next_cp = C;
+    auto checkpoint = [&](int tau, auto save) {
+        if (__builtin_expect(tau + 1 != next_cp, 1)) return;
+#pragma unroll
+        for (int c = 0; c < NC - 1; ++c)
+            if (next_cp == (c + 1) * C) save(c);
+        next_cp += C;
+    };
+    float rho_bd = INFINITY, dsum = 0.0f, s = 0.0f;  // the scoring wave's
+    bool limit = false;
+    if (w < ND) {
+        const VehConst<float> V = veh_f32(P);
+        const bool rear = MODEL == 0 && (lane & 1);
+        float st[6] = {0.0f, 0.0f, 0.0f, bs.vx0, bs.vy0, bs.om0};
+        int useen = 0, seen = 0;  // controls published; states every reader is past
+        for (int next = 0; next < N;) {
+            const int tau = __builtin_amdgcn_readfirstlane(next);
+            next = tau + 1;
+            auto all_read = [&]() {
+                const int a = min((int)sync[TS_READ], (int)sync[TS_READ + 1]);
+                return OPP_WAVE ? min(a, (int)sync[TS_READ + 2]) : a;
+            };
+            // (a poll for the controls refreshes the count of the free slots, too)
+            wait_for(tau, useen, [&]() {
+                const int a = sync[TS_U], b = all_read();
+                seen = __builtin_amdgcn_readfirstlane(b);
+                return a;
+            });
+            const float2 u = uring[(tau % TEAM_RING) * TEAM + i];
+            const StepConst<float> sc = step_const<MODEL, MathF32>(V, u.x, u.y);
+            if constexpr (MODEL == 0) rk4_pair<MathF32S>(V, sc, P.dt, st, rear);
+            else rk4<MODEL, MathF32>(V, sc, P.dt, st);
+            wait_for(tau - TEAM_RING, seen, all_read);
+            if (!rear) sring[(tau % TEAM_RING) * TEAM + i] = make_float4(st[0], st[1], st[2], st[3]);
+            publish(TS_S + w, tau + 1);
+            checkpoint(tau, [&](int c) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) cp[c][j] = st[j];
+            });
+        }
+        if (!rear) {
+#pragma unroll
+            for (int j = 0; j < 6; ++j) fin[(TF_ST + j) * TEAM + i] = st[j];
+        }
+    } else if (w == TEAM_CTRL) {
         const float2 *ubar = (const float2 *)(lds + L.ubar);
         const float4 *xref = (const float4 *)(lds + L.xref);
-        const float2 *opp = (const float2 *)(lds + L.opp);
-        const float4 *nodes = (const float4 *)(lds + L.nodes);
-        int seg = bs.seg0;
-        J = 0.0f;
-        rho_bd = INFINITY;
-        dsum = 0.0f;
-        s = 0.0f;
-#pragma unroll
-        for (int j = 0; j < MAXOPP; ++j) g2[j] = P.cap2;
-        limit = false;
-#pragma unroll
-        for (int c = 0; c < NC - 1; ++c) cseg[c] = 0;
+        const PhiloxLane pl = philox_lane(k, bs.ctr2, bs.ctr3, bs.key0, bs.key1);
         // controls of step t, in step order (one Philox call per pair of steps), published
         float2 zn = make_float2(0.0f, 0.0f);
-        int t_u = 0;
-        auto control = [&]() {
-            const int t = t_u++;
+        auto control = [&](int t) {
             float2 z;
             if ((t & 1) == 0) {
-                const uint4 r = philox4x32_10(make_uint4(k, (uint32_t)(t >> 1), bs.ctr2, bs.ctr3), bs.key0, bs.key1);
+                const uint4 r = philox_call<false>(pl, (uint32_t)(t >> 1), bs.key0, bs.key1);
                 z = gauss_pair(r.x, r.y);
                 zn = gauss_pair(r.z, r.w);
             } else {
                 z = zn;
             }
-            uring[(t % SPLIT_RING) * TS + i] = controls_k(P, bs, lds, L, k, t, ubar[t], z.x, z.y);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (lane == 0) uprod[w] = t + 1;
-        };
-        const int ahead0 = bs.N < SPLIT_AHEAD ? bs.N : SPLIT_AHEAD;
-        for (int t = 0; t < ahead0; ++t) control();
-        int seen = 0;  // the dynamics side's count as last read
-        float2 up = make_float2(0.0f, 0.0f);
-        for (int tau = 0; tau < bs.N; ++tau) {
-            if (tau + SPLIT_AHEAD < bs.N) control();
-            // reads that do not depend on this step's state go first (the step's control is
-            // still in its slot: it is rewritten SPLIT_RING - SPLIT_AHEAD iterations later)
-            const float2 u = uring[(tau % SPLIT_RING) * TS + i];
-            const float4 xr = xref[tau];
-            NodeAhead<NPF> ahead = read_ahead<NPF>(nodes, bs.W, seg);
-            const float2 *ot = opp + tau * (L.n_opp_max * (NDISC + 1));
-            float2 orow[MAXOPP * (NDISC + 1)];
-#pragma unroll
-            for (int j = 0; j < MAXOPP * (NDISC + 1); ++j) orow[j] = ot[j];
-            if (seen <= tau) {
-                for (int spin = 0; spin < P.spin_limit; ++spin) {
-                    seen = prod[w];
-                    if (seen > tau) break;
-                    __builtin_amdgcn_s_sleep(4);
-                }
-                stalled |= seen <= tau;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (noise_out) {
+                noise_out[2 * t] = z.x;
+                noise_out[2 * t + 1] = z.y;
             }
-            const float4 sv = ring[(tau % SPLIT_RING) * TS + i];
+            const float2 u = controls_k(P, bs, lds, L, k, t, ubar[t], z.x, z.y);
+            uring[(t % TEAM_RING) * TEAM + i] = u;
+            publish(TS_U, t + 1);
+            return u;
+        };
+        float J = 0.0f;
+        float2 up = make_float2(0.0f, 0.0f), u0 = control(0), u1 = N > 1 ? control(1) : u0;
+        int seen = 0;
+        for (int next = 0; next < N;) {
+            const int tau = __builtin_amdgcn_readfirstlane(next);
+            next = tau + 1;
+            float2 u2 = u1;
+            if (tau + TEAM_AHEAD < N) u2 = control(tau + TEAM_AHEAD);
+            const float4 xr = xref[tau];
+            wait_for(tau, seen, states);
+            const float4 sv = sring[(tau % TEAM_RING) * TEAM + i];
+            publish(TS_READ, tau + 1);
             const float st4[4] = {sv.x, sv.y, sv.z, sv.w};
+            // the terms summed in the one-lane order, so that both variants give the same bits
+            J += track_term(P, st4, xr);
+            J += ctrl_term(P, u0);
+            if (tau >= 1) J += rate_term(P, u0, up);
+            up = u0;
+            u0 = u1;
+            u1 = u2;
+        }
+        fin[TF_J * TEAM + i] = J;
+    } else if (w == TEAM_SCORE) {
+        const float4 *nodes = (const float4 *)(lds + L.nodes);
+        int seg = bs.seg0;
+        int seen = 0;
+        for (int next = 0; next < N;) {
+            const int tau = __builtin_amdgcn_readfirstlane(next);
+            next = tau + 1;
+            // reads that do not depend on this step's state go first
+            const NodeAhead<NPF> ahead = read_ahead<NPF>(nodes, bs.W, seg);
+            float2 orow[OROW];
+            if constexpr (!OPP_WAVE) opp_rows(tau, orow);
+            wait_for(tau, seen, states);
+            const float4 sv = sring[(tau % TEAM_RING) * TEAM + i];
+            publish(TS_READ + 1, tau + 1);
             const Foot f = project_ahead<NPF>(nodes, bs.W, P.max_moves, sv.x, sv.y, seg, ahead);
             seg = f.seg;
             limit |= f.limit;
             s = f.s;
-            // the terms summed in the one-lane order, so that both variants give the same bits
-            J += track_term(P, st4, xr);
-            J += ctrl_term(P, u);
-            if (tau >= 1) J += rate_term(P, u, up);
-            up = u;
             rho_bd = fminf(rho_bd, bound_term(f));
-            float ch = 1.0f, sh = 0.0f;
-            if (NDISC > 1) {
-                ch = fast_cos(sv.z);
-                sh = fast_sin(sv.z);
-            }
-            float ax[NDISC], ay[NDISC];
-            disc_centres<NDISC>(P, sv.x, sv.y, ch, sh, ax, ay);
-            int n_opp = bs.n_opp;
-            asm volatile("" : "+s"(n_opp));
-#pragma unroll
-            for (int j = 0; j < MAXOPP; ++j) {
-                if (j < n_opp)
-                    g2[j] = opp_min2<NDISC>(P, orow + j * (NDISC + 1), orow[j * (NDISC + 1)], sv.x, sv.y, ax, ay,
-                                            g2[j]);
-            }
-            if (tau + 1 > bs.N - bs.n_tail) dsum += f.d;
-            int Cv = C;
-            asm volatile("" : "+s"(Cv));
-#pragma unroll
-            for (int c = 0; c < NC - 1; ++c) {
-                if (tau + 1 == (c + 1) * Cv) cseg[c] = seg;
-            }
-            // the state is used: its ring entry may be overwritten
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (lane == 0) cons[w] = tau + 1;
+            if (tau + 1 > N - bs.n_tail) dsum += f.d;
+            if constexpr (!OPP_WAVE) opponents(tau, orow, sv);
+            checkpoint(tau, [&](int c) { cp[c][0] = __int_as_float(seg); });
         }
-        if (noise_out) {  // debug output only: the perturbations drawn again, outside the loop
-            for (int m = 0; 2 * m < bs.N; ++m) {
-                const uint4 r = philox4x32_10(make_uint4(k, (uint32_t)m, bs.ctr2, bs.ctr3), bs.key0, bs.key1);
-                const float2 z0 = gauss_pair(r.x, r.y), z1 = gauss_pair(r.z, r.w);
-                noise_out[4 * m] = z0.x;
-                noise_out[4 * m + 1] = z0.y;
-                if (2 * m + 1 < bs.N) {
-                    noise_out[4 * m + 2] = z1.x;
-                    noise_out[4 * m + 3] = z1.y;
-                }
-            }
+    } else {  // the opponents' wave
+        int seen = 0;
+        for (int next = 0; next < N;) {
+            const int tau = __builtin_amdgcn_readfirstlane(next);
+            next = tau + 1;
+            float2 orow[OROW];
+            opp_rows(tau, orow);
+            wait_for(tau, seen, states);
+            const float4 sv = sring[(tau % TEAM_RING) * TEAM + i];
+            publish(TS_READ + 2, tau + 1);
+            opponents(tau, orow, sv);
         }
+#pragma unroll
+        for (int j = 0; j < MAXOPP; ++j) fin[(TF_G2 + j) * TEAM + lane] = g2[j];
     }
+    if (lane == 0) sync[TS_STALL + w] = stalled ? 1 : 0;
     __syncthreads();
-    // one result object for both sides, written field by field
-    SampleResult res;
-    const float *fo = fin + i * SPLIT_FIN;  // the final state, read where it lies
-    if (dyn) {
-        res.cost = 0.0f;
-        res.viol = 0.0f;
-        res.h = false;
-        res.flags = 0;
+    SampleResult res{};
+    if (w == TEAM_SCORE) {
+        float st[6];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) res.st[j] = fo[j];
+        for (int j = 0; j < 6; ++j) st[j] = fin[(TF_ST + j) * TEAM + i];
+        if constexpr (OPP_WAVE) {
 #pragma unroll
-        for (int c = 0; c < NC - 1; ++c) {
-#pragma unroll
-            for (int j = 0; j < 6; ++j) res.cp[c][j] = cp[c][j];
-            res.cp[c][6] = 0.0f;
+            for (int j = 0; j < MAXOPP; ++j) g2[j] = fin[(TF_G2 + j) * TEAM + lane];
         }
-    } else {
-        const SampleResult t = terminal<MAXOPP>(P, bs, lds, L, J, rho_bd, dsum, s, g2, limit, fo);
-        res.cost = t.cost;
-        res.viol = t.viol;
-        res.h = t.h;
-        res.flags = t.flags;
-        if (stalled || fo[6] != 0.0f) {  // either side gave up a wait
+        res = terminal<MAXOPP>(P, bs, lds, L, fin[TF_J * TEAM + i], rho_bd, dsum, s, g2, limit, st);
+        // a wait of one of the sample's waves gave up
+        int gave = sync[TS_STALL + (ND == 2 ? i >> 5 : 0)] | sync[TS_STALL + TEAM_CTRL] | sync[TS_STALL + TEAM_SCORE];
+        if constexpr (OPP_WAVE) gave |= sync[TS_STALL + 1];
+        if (gave) {
             res.cost = __builtin_nanf("");
             res.viol = INFINITY;
             res.h = false;
-            res.flags = (unsigned char)((t.flags & 8) | 16);
+            res.flags = (unsigned char)((res.flags & 8) | 16);
             atomicOr(status, SGTP_STATUS_WAIT_GAVE_UP);
         }
-#pragma unroll
-        for (int j = 0; j < 6; ++j) res.st[j] = t.st[j];
-#pragma unroll
-        for (int c = 0; c < NC - 1; ++c) {
-#pragma unroll
-            for (int j = 0; j < 6; ++j) res.cp[c][j] = 0.0f;
-            res.cp[c][6] = __int_as_float(cseg[c]);
-        }
     }
+#pragma unroll
+    for (int c = 0; c < NC - 1; ++c)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) res.cp[c][j] = cp[c][j];
     return res;
 }
 
 template <int MODEL, int NDISC, int MAXOPP, int NPF, int LPS, int SPL>
 __device__ __forceinline__ SampleResult run_sample(const KParams &P, const BlockState &bs, char *lds,
                                                   const LdsLayout &L, uint32_t k, float *noise_out, bool rear,
-                                                  bool dyn, int *status) {
-    if constexpr (SPL != 0) return lane_sample_split<MODEL, NDISC, MAXOPP, NPF>(P, bs, lds, L, k, noise_out, dyn, status);
+                                                  int *status) {
+    if constexpr (SPL != 0) return lane_sample_team<MODEL, NDISC, MAXOPP, NPF>(P, bs, lds, L, k, noise_out, status);
     else return lane_sample<MODEL, NDISC, MAXOPP, NPF, LPS>(P, bs, lds, L, k, noise_out, rear);
 }
 
@@ -1705,31 +1755,38 @@ __device__ void reroll_block(const KParams &P, const LdsLayout &L, const BlockSt
 // ------------------------------------------------------------------------------
 // Kernels
 // ------------------------------------------------------------------------------
+// The item (last one whose first tile is at most `tile`) by a search over 64 candidates at a
+// time, one per lane: one or two dependent reads for any list (a bisection took nine of about
+// 0.25 us each, first touched by this workgroup's XCD, for the 378 vehicles of the evaluation).
 __device__ __forceinline__ int find_item(const ItemDev *items, int n, int tile) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (items[mid].tile0 <= tile) lo = mid; else hi = mid - 1;
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = n;
+    while (len > 1) {
+        const int step = (len + 63) / 64;
+        const bool in = lane * step < len;
+        const bool below = in && items[lo + (in ? lane * step : 0)].tile0 <= tile;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(below)) - 1;  // (the first candidate always is)
+        lo += c * step;
+        len = min(step, len - c * step);
     }
     return lo;
 }
 
 // Path-integral accumulation of one wave's samples (update = 1): score S = c + w_viol nu
-// (non-finite scores get no weight), weights exp(-(S - S_ref) / lambda) against the
+// (infinite where it gets no weight), weights exp(-(S - S_ref) / lambda) against the
 // wave's running reference S_ref, and the weighted sums of the sampled controls,
 // regenerated from the same Philox counters.  Lane l holds columns l and l + 64 of
-// (a_0, delta_0, a_1, delta_1, ...).
+// (a_0, delta_0, a_1, delta_1, ...).  Step pairs m0, m0 + ms, ... only (the team variant deals
+// them out to its waves).
 struct PiAcc {
     float S, w, c0, c1;
 };
 
 __device__ __forceinline__ void pi_accumulate(const KParams &P, const BlockState &bs, const char *lds,
-                                              const LdsLayout &L, uint32_t k, bool valid, const SampleResult &res,
-                                              PiAcc &a) {
+                                              const LdsLayout &L, uint32_t k, float S, PiAcc &a, int m0 = 0,
+                                              int ms = 1) {
     const int lane = threadIdx.x & 63;
-    float S = res.cost + P.w_viol * res.viol;
-    const bool fin = valid && isfinite(S);
-    S = fin ? S : INFINITY;
+    const bool fin = S < INFINITY;
     const float Sw = wave_min_f32(S);
     if (!(Sw < INFINITY)) return;  // uniform over the wave
     const float w = fin ? expf((Sw - S) * P.inv_lambda) : 0.0f;
@@ -1741,11 +1798,19 @@ __device__ __forceinline__ void pi_accumulate(const KParams &P, const BlockState
     a.c0 *= fa;
     a.c1 *= fa;
     const float2 *ubar = (const float2 *)(lds + L.ubar);
-    for (int m = 0; 2 * m < bs.N; ++m) {
-        const uint4 r = philox4x32_10(make_uint4(k, (uint32_t)m, bs.ctr2, bs.ctr3), bs.key0, bs.key1);
+    // the loop's parameters in vector registers: in scalar ones they were spilled and reloaded
+    // at every step pair where the workgroup also holds its queue's state
+    KParams Q = P;
+    Q.sigma_a = vreg(P.sigma_a); Q.sigma_d = vreg(P.sigma_d);
+    Q.a_min = vreg(P.a_min); Q.a_max = vreg(P.a_max); Q.d_min = vreg(P.d_min); Q.d_max = vreg(P.d_max);
+    const PhiloxLane pl = philox_lane(k, bs.ctr2, bs.ctr3, bs.key0, bs.key1);
+    for (int next = m0; 2 * next < bs.N;) {
+        const int m = __builtin_amdgcn_readfirstlane(next);
+        next = m + ms;
+        const uint4 r = philox_call<true>(pl, (uint32_t)m, bs.key0, bs.key1);
         const float2 z0 = gauss_pair(r.x, r.y), z1 = gauss_pair(r.z, r.w);
-        const float2 u0 = controls(P, ubar[2 * m], z0.x, z0.y);
-        const float2 u1 = (2 * m + 1 < bs.N) ? controls(P, ubar[2 * m + 1], z1.x, z1.y) : make_float2(0.0f, 0.0f);
+        const float2 u0 = controls(Q, ubar[2 * m], z0.x, z0.y);
+        const float2 u1 = (2 * m + 1 < bs.N) ? controls(Q, ubar[2 * m + 1], z1.x, z1.y) : make_float2(0.0f, 0.0f);
         const float v[4] = {wave_sum_f32(w * u0.x) * fb, wave_sum_f32(w * u0.y) * fb, wave_sum_f32(w * u1.x) * fb,
                             wave_sum_f32(w * u1.y) * fb};
 #pragma unroll
@@ -1768,67 +1833,76 @@ __device__ __forceinline__ void pi_accumulate(const KParams &P, const BlockState
 template <int MODEL, int NDISC, int MAXOPP, int NPF = 0, int LPS = 1, int SPL = 0>
 __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int item, const BlockState &bs, char *lds,
                                            int *s_last) {
-    constexpr int G = SPL ? 64 : 64 / LPS;  // samples per wave (per wave pair when split) = checkpoint group
-    constexpr int TS = SPL ? BLOCK / 2 : BLOCK;  // samples per pass of the workgroup (one lane each: LPS = 1)
+    constexpr int G = SPL ? TEAM : 64 / LPS;  // samples per wave (per team) = checkpoint group
     const bool rear = LPS == 2 && (threadIdx.x & 1);
-    const int vt = SPL ? split_vt(threadIdx.x) : (int)threadIdx.x;
-    const bool dyn = SPL && vt < BLOCK / 2;  // the split variant's dynamics lanes
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
+    const bool scoring = SPL ? wv == TEAM_SCORE : !rear;  // lanes that hold a sample's state and score
     const bool pi = A.P.update == 1;
     const int t0 = A.items[item].tile0;
     const int n_tiles_item = (item + 1 < A.n_items ? A.items[item + 1].tile0 : A.n_tiles) - t0;
     const int local_tile = tile - t0;
     const int pstride = 2 * A.L.N_max + 2;
     PiAcc pa{INFINITY, 0.0f, 0.0f, 0.0f};
-    for (int r = 0; r < A.spl; ++r) {
-        const uint32_t k = LPS == 1 ? (uint32_t)((local_tile * A.spl + r) * TS + (vt & (TS - 1)))
-                                    : (uint32_t)(local_tile * (BLOCK / 2) + (threadIdx.x >> 1));
+    const int spl = SPL || LPS > 1 ? 1 : A.spl;
+    for (int r = 0; r < spl; ++r) {
+        const uint32_t k = SPL        ? (uint32_t)(local_tile * TEAM + team_sample<MODEL>(threadIdx.x))
+                           : LPS == 1 ? (uint32_t)((local_tile * A.spl + r) * BLOCK + threadIdx.x)
+                                      : (uint32_t)(local_tile * (BLOCK / 2) + (threadIdx.x >> 1));
         const bool valid = k < (uint32_t)bs.K;
-        // (the split variant draws the perturbation on the scoring lane)
-        float *nz = (A.dbg_noise && valid && !rear && !dyn) ? A.dbg_noise + (size_t)k * bs.N * 2 : nullptr;
+        // (in a team, the wave of the controls draws the perturbation)
+        float *nz = (A.dbg_noise && valid && (SPL ? wv == TEAM_CTRL : !rear)) ? A.dbg_noise + (size_t)k * bs.N * 2 : nullptr;
         const SampleResult res =
-            run_sample<MODEL, NDISC, MAXOPP, NPF, LPS, SPL>(A.P, bs, lds, A.L, valid ? k : 0u, nz, rear, dyn, A.status);
-        unsigned long long key;
-        if (dyn) {
-            key = KEY_NONE;  // scored by the partner lane
-        } else if (pi) {
-            const float S = res.cost + A.P.w_viol * res.viol;
-            key = valid ? make_key(isfinite(S), isfinite(S) ? S : 0.0f, k) : KEY_NONE;
-        } else {
-            key = valid ? make_key(res.h, res.h ? res.cost : res.viol, k) : KEY_NONE;
+            run_sample<MODEL, NDISC, MAXOPP, NPF, LPS, SPL>(A.P, bs, lds, A.L, valid ? k : 0u, nz, rear, A.status);
+        float S = INFINITY;  // path-integral score
+        unsigned long long key = KEY_NONE;
+        if (!SPL || scoring) {
+            if (pi) {
+                S = res.cost + A.P.w_viol * res.viol;
+                key = valid ? make_key(isfinite(S), isfinite(S) ? S : 0.0f, k) : KEY_NONE;
+                S = valid && isfinite(S) ? S : INFINITY;
+            } else {
+                key = valid ? make_key(res.h, res.h ? res.cost : res.viol, k) : KEY_NONE;
+            }
         }
         const unsigned long long wmin = wave_min_u64(key);
-        const unsigned long long feas = __ballot(valid && res.h && !rear && !dyn);
+        const unsigned long long feas = __ballot(valid && res.h && scoring);
         if (lane == 0) {
             if (wmin != KEY_NONE) atomicMin(A.keys + bs.slot, wmin);
             const int cnt = __popcll(feas);
             if (cnt) atomicAdd(A.nfeas + bs.slot, cnt);
         }
         if (pi) {
-            pi_accumulate(A.P, bs, lds, A.L, valid ? k : 0u, valid && !dyn, res, pa);
-        } else if (SPL) {
-            // the scoring wave names its best lane; the two partner lanes export their parts
-            int *best = (int *)(lds + A.L.sp_sync) + 4;
-            if (!dyn) {
-                const unsigned long long b = __ballot(valid && key == wmin);
-                if (lane == 0) best[(vt >> 6) & 1] = (wmin != KEY_NONE && b) ? __builtin_ctzll(b) : -1;
+            if (SPL) {  // every wave of the team takes a share of the steps
+                float *sc = (float *)(lds + A.L.sp_fin);  // (its values are used)
+                if (scoring) sc[lane] = S;
+                __syncthreads();
+                const uint32_t kl = (uint32_t)(local_tile * TEAM + lane);
+                pi_accumulate(A.P, bs, lds, A.L, kl < (uint32_t)bs.K ? kl : 0u, sc[lane], pa, wv, BLOCK / 64);
+            } else {
+                pi_accumulate(A.P, bs, lds, A.L, valid ? k : 0u, S, pa);
             }
+        } else if (SPL) {
+            // the scoring wave names its best sample; the lanes that hold its parts export them
+            volatile int *best = (volatile int *)(lds + A.L.sp_sync) + TS_BEST;
+            const unsigned long long b = __ballot(valid && scoring && key == wmin);
+            if (scoring && lane == 0) *best = b ? __builtin_ctzll(b) : -1;
             __syncthreads();
-            if (valid && lane == best[(vt >> 6) & 1]) {
+            if (valid && (scoring || wv < (MODEL == 0 ? 2 : 1)) && team_sample<MODEL>(threadIdx.x) == *best) {
                 float *slot = A.cp_slots + ((size_t)A.items[item].group0 + k / G) * CP_FLOATS;
-                if (dyn) {  // states on the dynamics lane; segments and score on the scoring lane
 #pragma unroll
-                    for (int c = 0; c < ncp_of<NPF>() - 1; ++c)
+                for (int c = 0; c < ncp_of<NPF>() - 1; ++c) {
 #pragma unroll
-                        for (int i = 0; i < 6; ++i) slot[7 * c + i] = res.cp[c][i];
-                } else {
-#pragma unroll
-                    for (int c = 0; c < ncp_of<NPF>() - 1; ++c) slot[7 * c + 6] = res.cp[c][6];
+                    for (int i = 0; i < 6; ++i)
+                        if (!scoring) slot[7 * c + i] = res.cp[c][i];
+                    if (scoring) slot[7 * c + 6] = res.cp[c][0];
+                }
+                if (scoring) {
                     slot[CP_COST] = res.cost;
                     slot[CP_VIOL] = res.viol;
                 }
             }
-        } else if (valid && key == wmin && !rear) {  // the wave's best sample exports checkpoints and score
+        } else if (valid && key == wmin && scoring) {  // the wave's best sample exports checkpoints and score
             float *slot = A.cp_slots + ((size_t)A.items[item].group0 + k / G) * CP_FLOATS;
 #pragma unroll
             for (int c = 0; c < ncp_of<NPF>() - 1; ++c)
@@ -1837,7 +1911,7 @@ __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int it
             slot[CP_COST] = res.cost;
             slot[CP_VIOL] = res.viol;
         }
-        if (valid && !rear && !dyn) {
+        if (valid && scoring) {
             if (A.dbg_cost) A.dbg_cost[k] = res.cost;
             if (A.dbg_viol) A.dbg_viol[k] = res.viol;
             if (A.dbg_flags) A.dbg_flags[k] = res.flags;
@@ -1852,9 +1926,19 @@ __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int it
             }
         }
     }
-    if (pi) {  // the tile's partial: combine the four waves in order
+    if (pi && SPL) {  // the team's partial: columns 4 m .. 4 m + 3 from the wave that took step pair m
+        float *pp = A.pi_part + (size_t)tile * pstride;
+        if (threadIdx.x == 0) {
+            pp[0] = pa.S;
+            pp[1] = pa.w;
+        }
+        if (((lane >> 2) & 3) == wv) {
+            if (lane < 2 * bs.N) pp[2 + lane] = pa.c0;
+            if (lane + 64 < 2 * bs.N) pp[2 + lane + 64] = pa.c1;
+        }
+    } else if (pi) {  // the tile's partial: combine the four waves in order
         float *pw = (float *)(lds + A.L.rr_u);  // [4][2N + 2] (re-roll scratch, free here)
-        const int ws = 2 * bs.N + 2, wv = threadIdx.x >> 6;
+        const int ws = 2 * bs.N + 2;
         if (lane == 0) {
             pw[wv * ws] = pa.S;
             pw[wv * ws + 1] = pa.w;
@@ -1910,14 +1994,47 @@ __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int it
         float *sums = (float *)(lds + A.L.rr_u);  // [2N + 1]: sum of weights, weighted controls
         const float *pp = A.pi_part + (size_t)t0 * pstride;
         float Smin = INFINITY;
-        for (int t = 0; t < n_tiles_item; ++t) Smin = fminf(Smin, pp[(size_t)t * pstride]);
+        for (int t = lane; t < n_tiles_item; t += 64) Smin = fminf(Smin, pp[(size_t)t * pstride]);
+        Smin = wave_min_f32(Smin);
         pi_min = Smin;
         if (Smin < INFINITY) {
             if ((int)threadIdx.x < 2 * bs.N + 1) {
+                // teams: partials of pi_teams x 64 samples are formed first, then added in order
+                // like the others; read PB at a time (one by one, the 329 teams of 21000 samples
+                // took 0.04 ms per sweep longer)
+                constexpr int PB = 8;
+                const float *pc = pp + 1 + threadIdx.x;
                 float v = 0.0f;
-                for (int t = 0; t < n_tiles_item; ++t) {
-                    const float St = pp[(size_t)t * pstride];
-                    if (St < INFINITY) v += pp[(size_t)t * pstride + 1 + threadIdx.x] * expf((Smin - St) * A.P.inv_lambda);
+                auto add = [&](auto n_, const float *Sp, const float *vp) {
+                    constexpr int n = decltype(n_)::value;
+#pragma unroll
+                    for (int g = 0; g < PB; g += n) {
+                        float St = Sp[g], vt = 0.0f;
+#pragma unroll
+                        for (int j = 1; j < n; ++j) St = fminf(St, Sp[g + j]);
+#pragma unroll
+                        for (int j = 0; j < n; ++j)
+                            if (Sp[g + j] < INFINITY) vt += vp[g + j] * expf((St - Sp[g + j]) * A.P.inv_lambda);
+                        if (St < INFINITY) v += vt * expf((Smin - St) * A.P.inv_lambda);
+                    }
+                };
+                if (!SPL)
+                    for (int t = 0; t < n_tiles_item; ++t) {
+                        const float St = pp[(size_t)t * pstride];
+                        if (St < INFINITY) v += pc[(size_t)t * pstride] * expf((Smin - St) * A.P.inv_lambda);
+                    }
+                for (int t = 0; SPL && t < n_tiles_item; t += PB) {
+                    float Sp[PB], vp[PB];
+#pragma unroll
+                    for (int j = 0; j < PB; ++j) {
+                        const size_t o = (size_t)min(t + j, n_tiles_item - 1) * pstride;
+                        Sp[j] = pp[o];
+                        vp[j] = pc[o];
+                    }
+#pragma unroll
+                    for (int j = 0; j < PB; ++j) Sp[j] = t + j < n_tiles_item ? Sp[j] : INFINITY;
+                    if (A.pi_teams == 2) add(std::integral_constant<int, 2>{}, Sp, vp);
+                    else add(std::integral_constant<int, 4>{}, Sp, vp);
                 }
                 sums[threadIdx.x] = v;
             }
@@ -1960,7 +2077,7 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 
 // Sweep with one workgroup per tile.
 template <int MODEL, int NDISC, int MAXOPP, int NPF = 0, int LPS = 1, int SPL = 0>
-__global__ void __launch_bounds__(BLOCK, (NPF == 0 && LPS == 1 && SPL == 0) ? 4 : 1) k_sweep(LaunchArgs A) {
+__global__ void __launch_bounds__(BLOCK, SPL || (NPF == 0 && LPS == 1) ? 4 : 1) k_sweep(LaunchArgs A) {
     extern __shared__ __align__(16) char lds[];
     __shared__ int s_last;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -2026,7 +2143,7 @@ __global__ void __launch_bounds__(BLOCK, 4) k_sweep_persistent(LaunchArgs A) {
 // and the frame, with the same bits.  The second may read the unwrapped progress
 // before or after the first has updated it; both give the same lap count.
 template <int MODEL>
-__global__ void __launch_bounds__(BLOCK) k_setup(LaunchArgs A, int w_limit) {
+__global__ void __launch_bounds__(BLOCK) k_setup(LaunchArgs A, int w_limit, int w_rows) {
     extern __shared__ __align__(16) char lds[];
     __shared__ double red_v[BLOCK];
     __shared__ long long red_i[BLOCK];
@@ -2207,10 +2324,11 @@ __global__ void __launch_bounds__(BLOCK) k_setup(LaunchArgs A, int w_limit) {
     __syncthreads();
     const double c0 = sh[0], s0 = sh[1], psi0 = sh[2], sa = sh[3], lam = sh[4];
     const long long win0 = shl[0], W = shl[1], segl = shl[2];
+    const long long W_out = W < w_rows ? W : w_rows;  // rows a rollout can reach (the sweeps stage no more)
     if (roller) {
         // stage the float32 window and the nominal, roll the nominal out (predictions)
         float4 *nodes_l = (float4 *)(lds + A.L.nodes);
-        for (long long w = tid; w < W; w += BLOCK) {
+        for (long long w = tid; w < W_out; w += BLOCK) {
             double nd[NODE_STRIDE];
             node(win0 + w, nd);
             const double dx = nd[0] - px, dy = nd[1] - py;
@@ -2241,11 +2359,12 @@ __global__ void __launch_bounds__(BLOCK) k_setup(LaunchArgs A, int w_limit) {
     for (long long w = tid; w < W; w += BLOCK) {
         double nd[NODE_STRIDE];
         node(win0 + w, nd);
+        sv[w] = make_double2(nd[8], nd[7]);
+        if (w >= W_out) continue;
         const double dx = nd[0] - px, dy = nd[1] - py;
         const double nxl = c0 * nd[3] + s0 * nd[4], nyl = -s0 * nd[3] + c0 * nd[4];
         dst[2 * w] = make_float4((float)(c0 * dx + s0 * dy), (float)(-s0 * dx + c0 * dy), (float)nxl, (float)nyl);
         dst[2 * w + 1] = make_float4((float)nd[5], (float)nd[6], (float)(nd[8] - sa), 0.0f);
-        sv[w] = make_double2(nd[8], nd[7]);
     }
     __syncthreads();
     // 4. s^r recursion (thread 0, LDS only): s^r_{t+1} = s^r_t + dt lam v^r(s^r_t)
@@ -2696,38 +2815,63 @@ int check_params(sgtp_ctx *c, const sgtp_params *p) {
 struct Plan {  // host image of one launch sequence's descriptors
     std::vector<RaceDev> races;
     std::vector<ItemDev> all, ego, one;
-    int N_max = 0, n_opp_max = 0, w_max = 0, agents_total = 0;
+    int N_max = 0, n_opp_max = 0, w_max = 0, w_stage = 0, agents_total = 0;
     int tiles_all = 0, tiles_ego = 0;
     int lps = 1;          // lanes per sample
-    int split = 0;        // two waves per sample
-    int tile_samples = 0;  // samples per tile: BLOCK x samples per lane / lanes per sample
+    // per list: the team variant, and the samples per tile (TEAM, or BLOCK x samples per lane /
+    // lanes per sample)
+    int team_all = 0, team_ego = 0, team_one = 0;
+    int pi_teams = 4;
+    long long pi_all = 0;  // samples of all vehicles
+    int tile_all = 0, tile_ego = 0, tile_one = 0;
 };
 
-LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc);
+LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc, bool setup = false);
 int maxopp_bucket(int n_opp);
 constexpr int LDS_BUDGET = 58 * 1024;
 
+// Whether a launch over `samples` samples (its list's; `all`: every vehicle's) takes the team
+// variant: it is the faster one until the chip is full with one lane per sample.
+bool team_list(int nopp, long long samples) {
+    // up to the teams that are resident at once: four per CU (registers), three with the
+    // wider tables of more than 3 opponents (LDS).  One team more than that and a second
+    // round begins (10 vehicles, 65536 samples of the ego: 0.19 against 0.16 ms; 4 vehicles,
+    // 131072 samples: 0.29 against 0.17 ms).  Planning step with two waves per 64 samples, or
+    // one lane per sample beyond 3 opponents, before and now: 3 vehicles at K = 128 (N = 12)
+    // 0.172 -> 0.126 ms, 2 at 1024 (N = 20) 0.259 -> 0.201, 3 at 16384 (N = 40) 0.651 ->
+    // 0.576, 3 at 21800 (N = 40) 0.577 -> 0.396 (L = 2), 10 at 4000 (N = 40) 0.607 -> 0.379
+    // (L = 2); 126 games of 3 at K = 128 0.367 -> 0.230 ms.
+    return samples <= (nopp <= 3 ? TEAM_MAX_SAMPLES : TEAM_MAX_SAMPLES_WIDE);
+}
+
 int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_races, int spl, Plan &pl,
-                    int one_agent, bool allow_split, bool ctx_limits) {
+                    int one_agent, bool allow_team, bool ctx_limits) {
     if (!races || n_races < 1) return fail(c, SGTP_EINVAL, "no races");
     if (ctx_limits && n_races > c->max_races) return fail(c, SGTP_ESHAPE, "n_races exceeds the context");
-    // launches of about one wave per SIMD or fewer (at most 3 opponents, one sample per
-    // lane): the split variant where its rings fit in LDS, else the pair variant (dynamic
-    // model, feasibility selection); both measured faster than one lane per sample there,
-    // the split one the faster of the two
     {
-        long long samples = 0;
+        long long all = 0, ego = 0;
         int nopp = 0;
         for (int r = 0; r < n_races; ++r) {
-            samples += (long long)std::max(races[r].K, 0) * std::max(races[r].n_agents, 0);
+            const long long K = std::max(races[r].K, 0);
+            all += K * std::max(races[r].n_agents, 0);
+            ego += K;
             nopp = std::max(nopp, races[r].n_agents - 1);
         }
-        pl.split = (allow_split && spl == 1 && nopp <= 3 && samples <= SPLIT_MAX_SAMPLES) ? 1 : 0;
-        pl.lps = (!pl.split && spl == 1 && p->model == 0 && p->update == 0 && nopp <= 3 &&
-                  samples <= LPS2_MAX_SAMPLES) ? 2 : 1;
-        pl.tile_samples = BLOCK * spl / (pl.split ? 2 : pl.lps);
+        const long long one = std::max(races[0].K, 0);
+        const bool team = allow_team && spl == 1;
+        pl.team_all = team && team_list(nopp, all);
+        pl.team_ego = team && team_list(nopp, ego);
+        pl.team_one = team && team_list(nopp, one);
+        // where the team's rings do not fit in LDS: a pair of lanes per sample up to about one
+        // wave per SIMD (dynamic model, feasibility selection, at most 3 opponents)
+        pl.lps = (!allow_team && spl == 1 && p->model == 0 && p->update == 0 && nopp <= 3 &&
+                  all <= LPS2_MAX_SAMPLES) ? 2 : 1;
+        pl.pi_all = all;
+        pl.tile_all = pl.team_all ? TEAM : BLOCK * spl / pl.lps;
+        pl.tile_ego = pl.team_ego ? TEAM : BLOCK * spl / pl.lps;
+        pl.tile_one = pl.team_one ? TEAM : BLOCK * spl / pl.lps;
     }
-    const int gsz = 64 / pl.lps;  // samples per wave (per wave pair when split) = checkpoint group
+    const int gsz = 64 / pl.lps;  // samples per wave (per team) = checkpoint group
     int slot = 0;
     long long group_total = 0;
     double wneed = 0;
@@ -2752,7 +2896,7 @@ int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, i
         if (p->update == 1 && s.prop && s.K_prop > 0)
             return fail(c, SGTP_EINVAL, "a learned proposal cannot be combined with the path-integral update");
         pl.races.push_back(d);
-        const int tiles = (s.K + pl.tile_samples - 1) / pl.tile_samples;
+        const int tiles = (s.K + pl.tile_all - 1) / pl.tile_all;
         const long long groups = (s.K + gsz - 1) / gsz;
         for (int i = 0; i < s.n_agents; ++i) {
             ItemDev it{r, i, slot + i, pl.tiles_all, (int)(group_total + i * groups), 0};
@@ -2766,7 +2910,7 @@ int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, i
             if (i == s.ego) {
                 ItemDev e = it;
                 e.tile0 = pl.tiles_ego;
-                pl.tiles_ego += tiles;
+                pl.tiles_ego += (s.K + pl.tile_ego - 1) / pl.tile_ego;
                 pl.ego.push_back(e);
             }
         }
@@ -2787,19 +2931,35 @@ int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, i
         return fail(c, SGTP_ESHAPE, "tiles exceed the path-integral buffer");
     pl.agents_total = slot;
     pl.w_max = (int)std::min<double>(WIN_MAX, wneed);
+    // a sample's segment moves at most max_moves nodes per step, so no sweep reads past that
+    // (rows read ahead included).  Where the bound halves the window at least -- long curved
+    // windows of fine racelines: 248 of 1432 rows at the paper's scale, 8 instead of 46 KB of
+    // LDS per workgroup -- a sweep stages only these rows.
+    const double reach = WIN_BACK + (double)p->max_moves * pl.N_max + 8.0;
+    pl.w_stage = 2.0 * reach <= pl.w_max ? (int)reach : pl.w_max;
     return SGTP_OK;
 }
 
-// The plan of one launch sequence; the split variant only where its LDS ring fits.
+// The plan of one launch sequence; the team variant only where its LDS rings fit.
 int build_plan(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_races, int spl, Plan &pl,
                int one_agent = -1, bool ctx_limits = true) {
     int rc = build_plan_once(c, p, races, n_races, spl, pl, one_agent, true, ctx_limits);
-    if (rc || !pl.split || make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc).total <= LDS_BUDGET) return rc;
+    // The order of the path-integral sums is part of their result: partial sums over 128
+    // samples up to PI_128_MAX_SAMPLES and 3 opponents (where tables of this many bytes fit),
+    // over BLOCK samples otherwise.
+    constexpr long long PI_128_MAX_SAMPLES = 65536;
+    constexpr int PI_128_BYTES = 16416;
+    const bool by_128 = !rc && pl.pi_all <= PI_128_MAX_SAMPLES && pl.n_opp_max <= 3 &&
+                        make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc, true).total + PI_128_BYTES <= LDS_BUDGET;
+    pl.pi_teams = by_128 ? 2 : 4;
+    if (rc || !(pl.team_all || pl.team_ego || pl.team_one) ||
+        make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc).total_team <= LDS_BUDGET)
+        return rc;
     pl = Plan();
     return build_plan_once(c, p, races, n_races, spl, pl, one_agent, false, ctx_limits);
 }
 
-LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc) {
+LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc, bool setup) {
     LdsLayout L{};
     int off = 0;
     auto take = [&](int bytes) {
@@ -2810,12 +2970,13 @@ LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc) {
     L.N_max = pl.N_max;
     L.n_opp_max = std::max(1, maxopp);
     L.w_max = pl.w_max;
+    L.w_stage = setup ? pl.w_max : pl.w_stage;
     L.ubar = take(pl.N_max * 8);
     L.xref = take(pl.N_max * 16);
     L.oppT = take(L.n_opp_max * 16);
     L.oppc = take(L.n_opp_max * 16);
     L.opp = take(pl.N_max * L.n_opp_max * (ndisc + 1) * 8);
-    L.nodes = take(pl.w_max * 32);
+    L.nodes = take(L.w_stage * 32);
     L.prop = take(pl.N_max * 16);
     // rr_u..rr_f also hold the path-integral partials of a tile's four waves,
     // 4 x (2N + 2) floats, which fit for every N >= 1
@@ -2824,13 +2985,12 @@ LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc) {
     L.rr_f = take(pl.N_max * 16);
     L.rr_t = take(pl.N_max * 16);
     L.rr_sync = take(NCP_MAX * 4);
-    if (pl.split) {
-        L.sp_ring = take(SPLIT_RING * (BLOCK / 2) * 16);
-        L.sp_uring = take(SPLIT_RING * (BLOCK / 2) * 8);
-        L.sp_sync = take(8 * 4);            // prod[2], cons[2], best lane[2], uprod[2]
-        L.sp_fin = take((BLOCK / 2) * SPLIT_FIN * 4);  // per sample: final state
-    }
     L.total = off;
+    L.sp_uring = take(TEAM_RING * TEAM * 8);
+    L.sp_sring = take(TEAM_RING * TEAM * 16);
+    L.sp_sync = take(TS_WORDS * 4);
+    L.sp_fin = take((TF_G2 + L.n_opp_max) * TEAM * 4);
+    L.total_team = off;
     return L;
 }
 
@@ -2884,9 +3044,9 @@ void launch_sweep_t(const LaunchArgs &A, int grid, hipStream_t st, int *occ) {
     } else if (grid == 0) {
         // about one wave per SIMD or fewer (small games): the latency variant reads ahead
         constexpr int LAT_WAVES = 1536;
-        if (MAXOPP <= 3 && A.split)
-            hipLaunchKernelGGL((k_sweep<MODEL, NDISC, MAXOPP <= 3 ? MAXOPP : 3, 6, 1, 1>), dim3(A.n_tiles),
-                               dim3(BLOCK), A.L.total, st, A);
+        if (A.team)
+            hipLaunchKernelGGL((k_sweep<MODEL, NDISC, MAXOPP, 6, 1, 1>), dim3(A.n_tiles), dim3(BLOCK),
+                               A.L.total_team, st, A);
         else if (MODEL == 0 && MAXOPP <= 3 && A.lps == 2)
             hipLaunchKernelGGL((k_sweep<0, NDISC, MAXOPP <= 3 ? MAXOPP : 3, 6, 2>), dim3(A.n_tiles), dim3(BLOCK),
                                A.L.total, st, A);
@@ -2922,7 +3082,7 @@ void dispatch_sweep(int model, int ndisc, int mo, const LaunchArgs &A, hipStream
 // Order the items of a sweep for the persistent kernel: vehicles go to NQ queues
 // by longest-processing-time first (work = K N), each queue is a contiguous run of
 // tiles, heaviest vehicles first inside a queue.
-void layout_queues(const Plan &pl, std::vector<ItemDev> &items, int q_begin[NQ], int q_len[NQ]) {
+void layout_queues(const Plan &pl, std::vector<ItemDev> &items, int tile_samples, int q_begin[NQ], int q_len[NQ]) {
     std::vector<int> order(items.size());
     for (size_t i = 0; i < items.size(); ++i) order[i] = (int)i;
     auto work = [&](const ItemDev &it) {
@@ -2948,12 +3108,20 @@ void layout_queues(const Plan &pl, std::vector<ItemDev> &items, int q_begin[NQ],
             ItemDev it = items[i];
             it.tile0 = tile;
             const RaceDev &r = pl.races[it.race];
-            tile += (r.K + pl.tile_samples - 1) / pl.tile_samples;
+            tile += (r.K + tile_samples - 1) / tile_samples;
             out.push_back(it);
         }
         q_len[q] = tile - q_begin[q];
     }
     items = out;
+}
+
+void launch_setup(int model, LaunchArgs a, const LdsLayout &L, const Plan &pl, hipStream_t st) {
+    a.L = L;
+    if (model == 0)
+        hipLaunchKernelGGL(k_setup<0>, dim3(2 * a.n_items), dim3(BLOCK), L.total, st, a, pl.w_max, pl.w_stage);
+    else
+        hipLaunchKernelGGL(k_setup<1>, dim3(2 * a.n_items), dim3(BLOCK), L.total, st, a, pl.w_max, pl.w_stage);
 }
 
 struct Runner {
@@ -2977,7 +3145,8 @@ struct Runner {
         A.P = make_kparams(p);
         A.P.spin_limit = c->spin_limit;
         A.L = make_layout(pl, mo, p->n_disc);
-        if (A.L.total > LDS_BUDGET) return fail(c, SGTP_ESHAPE, "staged tables exceed the LDS budget");
+        if (make_layout(pl, mo, p->n_disc, true).total > LDS_BUDGET)
+            return fail(c, SGTP_ESHAPE, "staged tables exceed the LDS budget");
         rc = upload_plan(c, pl, st, &d_races, &d_all, &d_ego, &d_one);
         if (rc) return rc;
         A.tracks = c->d_tracks;
@@ -2993,7 +3162,7 @@ struct Runner {
         A.status = c->d_status;
         A.spl = 1;
         A.lps = pl.lps;
-        A.split = pl.split;
+        A.pi_teams = pl.pi_teams;
         pred[0] = c->d_pred[0];
         pred[1] = c->d_pred[1];
         return SGTP_OK;
@@ -3012,7 +3181,8 @@ struct Runner {
         A.P = make_kparams(p);
         A.P.spin_limit = c->spin_limit;
         A.L = make_layout(pl, mo, p->n_disc);
-        if (A.L.total > LDS_BUDGET) return fail(c, SGTP_ESHAPE, "staged tables exceed the LDS budget");
+        if (make_layout(pl, mo, p->n_disc, true).total > LDS_BUDGET)
+            return fail(c, SGTP_ESHAPE, "staged tables exceed the LDS budget");
         const NoallocLayout S = noalloc_layout();
         DescImage img{};
         img.race = pl.races[0];
@@ -3039,7 +3209,7 @@ struct Runner {
         A.status = c->d_status;
         A.spl = 1;
         A.lps = pl.lps;
-        A.split = pl.split;
+        A.pi_teams = pl.pi_teams;
         pred[0] = (float *)(base + S.pred0);
         pred[1] = (float *)(base + S.pred1);
         allow_timing = false;
@@ -3051,22 +3221,20 @@ struct Runner {
         a.items = d_all;
         a.n_items = (int)pl.all.size();
         a.pred_out = pred[0];
-        if (p->model == 0)
-            hipLaunchKernelGGL(k_setup<0>, dim3(2 * a.n_items), dim3(BLOCK), A.L.total, st, a, pl.w_max);
-        else
-            hipLaunchKernelGGL(k_setup<1>, dim3(2 * a.n_items), dim3(BLOCK), A.L.total, st, a, pl.w_max);
+        launch_setup(p->model, a, make_layout(pl, mo, p->n_disc, true), pl, st);
         HIPCHK(c, hipGetLastError());
         return SGTP_OK;
     }
     // one sweep over `items` reading predictions pred[par]; the selected samples are
     // re-rolled in the same launch and write pred[par ^ 1]
-    int sweep(const ItemDev *items, const std::vector<ItemDev> &host_items, int n_tiles, int phase, int par,
+    int sweep(const ItemDev *items, const std::vector<ItemDev> &host_items, int n_tiles, int team, int phase, int par,
               sgtp_choice *choice, int choice_base, int adopt, int final_mode, float *u_apply,
               const LaunchArgs *dbg = nullptr) {
         LaunchArgs a = dbg ? *dbg : A;
         a.items = items;
         a.n_items = (int)host_items.size();
         a.n_tiles = n_tiles;
+        a.team = team;
         a.phase = phase;
         a.pred_in = pred[par];
         a.pred_out = pred[par ^ 1];
@@ -3133,10 +3301,7 @@ int plan_enqueue(sgtp_plan *P, hipStream_t st) {
     a.pred_out = c->d_pred[0];
     a.qreset = P->d_qctr;
     a.n_qreset = (P->L + 2) * NQ;
-    if (P->p.model == 0)
-        hipLaunchKernelGGL(k_setup<0>, dim3(2 * a.n_items), dim3(BLOCK), a.L.total, st, a, P->pl.w_max);
-    else
-        hipLaunchKernelGGL(k_setup<1>, dim3(2 * a.n_items), dim3(BLOCK), a.L.total, st, a, P->pl.w_max);
+    launch_setup(P->p.model, a, make_layout(P->pl, P->mo, P->p.n_disc, true), P->pl, st);
     HIPCHK(c, hipGetLastError());
     const int nt = P->pl.agents_total;
     if (P->mlp) {  // learned proposal: features -> network -> tables, before the first sweep
@@ -3155,6 +3320,7 @@ int plan_enqueue(sgtp_plan *P, hipStream_t st) {
         w.items = ego ? P->d_ego : P->d_all;
         w.n_items = (int)(ego ? P->pl.ego.size() : P->pl.all.size());
         w.n_tiles = ego ? P->pl.tiles_ego : P->pl.tiles_all;
+        w.team = ego ? P->pl.team_ego : P->pl.team_all;
         w.phase = ph;
         w.pred_in = c->d_pred[ph & 1];
         w.pred_out = c->d_pred[(ph & 1) ^ 1];
@@ -3168,7 +3334,7 @@ int plan_enqueue(sgtp_plan *P, hipStream_t st) {
             w.q_begin[q] = ego ? P->qb_ego[q] : P->qb_all[q];
             w.q_len[q] = ego ? P->ql_ego[q] : P->ql_all[q];
         }
-        const int grid = P->opt.persistent ? (ego ? P->grid_ego : P->grid_all) : 0;
+        const int grid = P->opt.persistent && !w.team ? (ego ? P->grid_ego : P->grid_all) : 0;
         const bool timed = c->timing && !P->capturing;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) {
@@ -3324,8 +3490,8 @@ int sgtp_ctx_set_poll_limit(sgtp_ctx *c, int polls) {
 int sgtp_ctx_enable_path_integral(sgtp_ctx *c) {
     if (!c) return SGTP_EINVAL;
     if (c->d_pi) return SGTP_OK;
-    // tiles of BLOCK / 2 samples (the split variant), one partial tile per vehicle
-    const long long tiles = c->max_groups / (BLOCK / 128) + c->max_agents;
+    // tiles of BLOCK samples, or of TEAM in the launches small enough for teams
+    const long long tiles = std::max(c->max_groups / 2, TEAM_MAX_SAMPLES / TEAM) + c->max_agents;
     const size_t bytes = sizeof(float) * (size_t)tiles * (size_t)(2 * c->max_N + 2);
     if (hipMalloc((void **)&c->d_pi, bytes) != hipSuccess) {
         c->d_pi = nullptr;
@@ -3396,8 +3562,8 @@ int sgtp_rollout_cost(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *race, 
     dbg.dbg_viol = viol;
     dbg.dbg_xfinal = x_final;
     dbg.dbg_noise = noise;
-    const int tiles = (race->K + r.pl.tile_samples - 1) / r.pl.tile_samples;
-    return r.sweep(r.d_one, r.pl.one, tiles, phase, 0, out, r.pl.all[agent].slot, 0, 0, nullptr, &dbg);
+    const int tiles = (race->K + r.pl.tile_one - 1) / r.pl.tile_one;
+    return r.sweep(r.d_one, r.pl.one, tiles, r.pl.team_one, phase, 0, out, r.pl.all[agent].slot, 0, 0, nullptr, &dbg);
 }
 
 int sgtp_rollout_cost_noalloc(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *race, int agent, int phase,
@@ -3425,8 +3591,8 @@ int sgtp_rollout_cost_noalloc(sgtp_ctx *c, const sgtp_params *p, const sgtp_race
     dbg.dbg_viol = viol;
     dbg.dbg_xfinal = x_final;
     dbg.dbg_noise = noise;
-    const int tiles = (race->K + r.pl.tile_samples - 1) / r.pl.tile_samples;
-    return r.sweep(r.d_one, r.pl.one, tiles, phase, 0, out, r.pl.all[agent].slot, 0, 0, nullptr, &dbg);
+    const int tiles = (race->K + r.pl.tile_one - 1) / r.pl.tile_one;
+    return r.sweep(r.d_one, r.pl.one, tiles, r.pl.team_one, phase, 0, out, r.pl.all[agent].slot, 0, 0, nullptr, &dbg);
 }
 
 int sgtp_gauss_pairs(const unsigned int *r_even, const unsigned int *r_odd, float *out, int n, void *stream) {
@@ -3446,8 +3612,8 @@ int sgtp_ibr_sweep(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, in
     if (rc) return rc;
     rc = r.setup_all();
     if (rc) return rc;
-    if (ego_only) return r.sweep(r.d_ego, r.pl.ego, r.pl.tiles_ego, phase, 0, out, 0, 1, 0, nullptr);
-    return r.sweep(r.d_all, r.pl.all, r.pl.tiles_all, phase, 0, out, 0, 1, 0, nullptr);
+    if (ego_only) return r.sweep(r.d_ego, r.pl.ego, r.pl.tiles_ego, r.pl.team_ego, phase, 0, out, 0, 1, 0, nullptr);
+    return r.sweep(r.d_all, r.pl.all, r.pl.tiles_all, r.pl.team_all, phase, 0, out, 0, 1, 0, nullptr);
 }
 
 int sgtp_plan_step(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_races, int L_ibr, float *u_apply,
@@ -3466,9 +3632,9 @@ int sgtp_plan_step(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, in
         const int final_mode = ego ? 2 : (ph == L_ibr ? 1 : 0);
         sgtp_choice *tr = trace ? trace + (size_t)ph * nt : nullptr;
         if (ego)
-            rc = r.sweep(r.d_ego, r.pl.ego, r.pl.tiles_ego, ph, ph & 1, tr, 0, 1, final_mode, u_apply);
+            rc = r.sweep(r.d_ego, r.pl.ego, r.pl.tiles_ego, r.pl.team_ego, ph, ph & 1, tr, 0, 1, final_mode, u_apply);
         else
-            rc = r.sweep(r.d_all, r.pl.all, r.pl.tiles_all, ph, ph & 1, tr, 0, 1, final_mode, u_apply);
+            rc = r.sweep(r.d_all, r.pl.all, r.pl.tiles_all, r.pl.team_all, ph, ph & 1, tr, 0, 1, final_mode, u_apply);
         if (rc) return rc;
     }
     return SGTP_OK;
@@ -3530,10 +3696,10 @@ int sgtp_plan_create(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, 
         delete P;
         return rc;
     }
-    // the pair and split variants run one workgroup per tile
-    if (P->pl.lps == 2 || P->pl.split) P->opt.persistent = o.persistent = 0;
-    layout_queues(P->pl, P->pl.all, P->qb_all, P->ql_all);
-    layout_queues(P->pl, P->pl.ego, P->qb_ego, P->ql_ego);
+    // the pair and team variants run one workgroup per tile
+    if (P->pl.lps == 2 || P->pl.team_all) P->opt.persistent = o.persistent = 0;
+    layout_queues(P->pl, P->pl.all, P->pl.tile_all, P->qb_all, P->ql_all);
+    layout_queues(P->pl, P->pl.ego, P->pl.tile_ego, P->qb_ego, P->ql_ego);
     P->pl.tiles_all = P->ql_all[NQ - 1] + P->qb_all[NQ - 1];
     P->pl.tiles_ego = P->ql_ego[NQ - 1] + P->qb_ego[NQ - 1];
     P->mo = maxopp_bucket(P->pl.n_opp_max);
@@ -3541,7 +3707,7 @@ int sgtp_plan_create(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, 
     A.P = make_kparams(p);
     A.P.spin_limit = c->spin_limit;
     A.L = make_layout(P->pl, P->mo, p->n_disc);
-    if (A.L.total > LDS_BUDGET) {
+    if (make_layout(P->pl, P->mo, p->n_disc, true).total > LDS_BUDGET) {
         delete P;
         return fail(c, SGTP_ESHAPE, "staged tables exceed the LDS budget");
     }
@@ -3576,7 +3742,7 @@ int sgtp_plan_create(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, 
     A.status = c->d_status;
     A.spl = o.samples_per_lane;
     A.lps = P->pl.lps;
-    A.split = P->pl.split;
+    A.pi_teams = P->pl.pi_teams;
     A.chunk = o.tiles_per_fetch;
     if (o.persistent) {
         int occ = 1, dev = 0, cus = 0;
@@ -3654,7 +3820,7 @@ int sgtp_plan_info(const sgtp_plan *P, int *grid_sweep, int *tiles_sweep, int *l
     if (!P) return SGTP_EINVAL;
     if (grid_sweep) *grid_sweep = P->opt.persistent ? P->grid_all : P->pl.tiles_all;
     if (tiles_sweep) *tiles_sweep = P->pl.tiles_all;
-    if (lds_bytes) *lds_bytes = P->base.L.total;
+    if (lds_bytes) *lds_bytes = P->pl.team_all ? P->base.L.total_team : P->base.L.total;
     return SGTP_OK;
 }
 

@@ -1,5 +1,6 @@
 """The throughput variant of the sweep (one lane per sample, several waves per SIMD) against
-the small-launch variant, bit for bit, where its own code differs: the batched raceline walk
+the small-launch variant (64 samples on the four waves of a workgroup, both vehicle models,
+up to and beyond three opponents), bit for bit, where its own code differs: the batched raceline walk
 (fine nodes: many nodes per step; few moves allowed: the walk's limit; the end of an open
 track: the window's limit), the screening of the opponents in groups (every remainder of a
 group), the clip without its NaN test (a NaN and an infinite nominal control) and the
@@ -14,7 +15,7 @@ from paper_2607_25388_amd import inputs
 pytestmark = pytest.mark.gpu
 
 OUT = ("cost", "viol", "flags", "x_final", "noise")
-K_LARGE, K_SMALL = 100000, 1500  # more than 1536 waves against one workgroup per 64 or 128 samples
+K_LARGE, K_SMALL = 100000, 1500  # more than 1536 waves against one workgroup per 64 samples
 
 
 @pytest.fixture(scope="module")
@@ -36,6 +37,8 @@ def _case(name):
         over = dict(max_moves=1)
     elif name == "open_end":
         track = inputs.make_straight_track(120.0, 10.0, vref=40.0)
+    elif name.startswith("kinematic"):
+        n, N, over = int(name[9:]), 17, dict(model=1)
     elif name.startswith("vehicles"):
         n, N = int(name[8:]), 25
     params = dict(inputs.default_params(N, 3), **over)
@@ -55,7 +58,8 @@ def _case(name):
 
 @pytest.mark.parametrize("name", ["plain", "fine_nodes", "two_moves", "one_move", "open_end", "nan_nominal",
                                   "inf_nominal", "proposal", "vehicles1", "vehicles2", "vehicles4", "vehicles5",
-                                  "vehicles6", "vehicles7", "vehicles10"])
+                                  "vehicles6", "vehicles7", "vehicles10", "kinematic1", "kinematic3",
+                                  "kinematic6"])
 def test_throughput_variant_matches_small_launch_variant(planner, name):
     import torch
     track, race, params = _case(name)
