@@ -44,7 +44,7 @@ constexpr size_t P_W1 = 0, P_B1 = P_W1 + (size_t)D_IN * D_H, P_W2 = P_B1 + D_H, 
                  P_W3 = P_B2 + D_H, P_B3 = P_W3 + (size_t)D_H * D_OUT, P_TOTAL = P_B3 + D_OUT;
 
 // ------------------------------------------------------------------------------
-// BF16 MFMA GEMM: C[m][n] = sum_k A(m, k) B(k, n) (+ bias[n]); optional GELU copy in BF16.
+// BF16 MFMA GEMM: C[m][n] = sum_k A(m, k) B(k, n) (+ bias[n]).
 // A(m, k) = A[m a_m + k a_k], B(k, n) = B[k b_k + n b_n] (any strides, so transposed
 // operands need no copies).  Workgroup tile 64 x 64; each of the 4 waves owns a 32 x 32
 // quarter as 2 x 2 MFMA tiles of 16 x 16 x 32.  K runs in chunks of 64 through two LDS
@@ -62,12 +62,9 @@ struct GemmArgs {
     long long b_k, b_n;
     int M, N, K;
     const float *bias;  // [N] or NULL
-    float *C;           // [M][ldc] float32 result (pre-activation), or NULL
+    float *C;           // [M][ldc] float32 result
     long long ldc;
     long long c_split;  // split K: slice z writes its partial product to C + z c_split
-    bf16 *H;            // [M][ldh] BF16 GELU(result) -- or, with gpre, BF16 result x GELU'(gpre) -- or NULL
-    long long ldh;
-    const float *gpre;  // [M][ldh] pre-activations for the activation-gradient output, or NULL
     int a_mode, b_mode; // operand staging: STAGE_ELEM, STAGE_VEC_K or STAGE_VEC_ROW
     int ones_row;       // row index of A that reads as 1 for every k (a bias gradient), or -1
 };
@@ -221,10 +218,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, int bx, int by, int
                         continue;
                     }
                     if (g.bias) x += g.bias[n];
-                    if (g.C) g.C[(long long)m * g.ldc + n] = x;
-                    if (g.H)
-                        g.H[(long long)m * g.ldh + n] =
-                            g.gpre ? (bf16)(x * gelu_grad_f(g.gpre[(long long)m * g.ldh + n])) : (bf16)gelu_f(x);
+                    g.C[(long long)m * g.ldc + n] = x;
                 }
             }
 }
@@ -233,15 +227,159 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
     gemm_tile(g, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
 }
 
+// ------------------------------------------------------------------------------
+// The same product in large tiles, for operands with a unit stride along k (AVK, BVK) or along
+// their rows, read as vectors of 8 (of any alignment: 2-byte aligned vector loads).  A BM x BN workgroup tile, WM x WN per wave, K in chunks of
+// 64 through two LDS buffers.  LDS holds [row][64 k] without padding, the eight 16-byte
+// pieces of a row permuted by the row (lds_piece), so that neither the fragments' reads (16
+// consecutive rows, one piece) nor the staging writes meet in a bank.  An operand with the
+// unit stride along its rows is read as blocks of 8 rows x NV k and turned in registers (one 8-byte LDS store
+// per row instead of 2-byte ones).  The product is formed transposed (the B fragment in the
+// MFMA's first place), which leaves four consecutive columns of one row in a lane: one
+// 16-byte store.  Every output is accumulated over the same blocks of 32 k in the same order
+// as in gemm_tile, so the results are the same bits.
+// ------------------------------------------------------------------------------
+__device__ __forceinline__ int lds_piece(int row, int c) { return row * 64 + 8 * (c ^ ((row ^ (row >> 3)) & 7)); }
+
+// NV vectors of one thread: BR rows x 64 k of an operand from row r0 and k0 on (zero beyond R
+// and K).  VK (unit stride along k): vector i is row (tid + NT i) / 8, k 8 ((tid + NT i) % 8)
+// .. + 7; otherwise k NV (tid / (BR / 8)) + i, rows 8 (tid % (BR / 8)) .. + 7.
+typedef u16x8 __attribute__((aligned(2))) u16x8_any;
+template <int BR, int NT, bool VK, int NV = BR * 8 / NT>
+__device__ __forceinline__ void load_tile(const bf16 *__restrict__ P, long long s_r, long long s_k, int r0, int R,
+                                          int k0, int K, int tid, u16x8 (&v)[NV]) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int r = VK ? r0 + ((tid + NT * i) >> 3) : r0 + 8 * (tid % (BR / 8));
+        const int k = VK ? k0 + 8 * (tid & 7) : k0 + NV * (tid / (BR / 8)) + i;
+        const bf16 *p = P + (long long)r * s_r + (long long)k * s_k;
+        if (VK ? r < R && k + 8 <= K : k < K && r + 8 <= R) {
+            v[i] = *(const u16x8_any *)p;
+        } else {
+            u16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (VK ? r < R && k + j < K : k < K && r + j < R) x[j] = __builtin_bit_cast(unsigned short, p[j]);
+            v[i] = x;
+        }
+    }
+}
+template <int BR, int NT, bool VK, int NV = BR * 8 / NT>
+__device__ __forceinline__ void store_tile(bf16 *S, int tid, const u16x8 (&v)[NV]) {
+    typedef unsigned short u16xn __attribute__((ext_vector_type(NV)));
+    if constexpr (VK) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int q = tid + NT * i;
+            *(u16x8 *)&S[lds_piece(q >> 3, q & 7)] = v[i];
+        }
+    } else {
+        const int k = NV * (tid / (BR / 8));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            u16xn x;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) x[i] = v[i][j];
+            *(u16xn *)&S[lds_piece(8 * (tid % (BR / 8)) + j, k >> 3) + (k & 7)] = x;
+        }
+    }
+}
+
+template <int BM, int BN, int WM, int WN, bool AVK, bool BVK>
+__global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN)) k_gemm_big(GemmArgs g, int gx) {
+    constexpr int NT = 64 * (BM / WM) * (BN / WN), TI = WM / 16, TJ = WN / 16;
+    constexpr int NVA = BM * 8 / NT, NVB = BN * 8 / NT;
+    __shared__ __align__(16) bf16 As[2][BM * GK];
+    __shared__ __align__(16) bf16 Bs[2][BN * GK];
+    // workgroups go to the XCDs round-robin: each XCD takes one run of consecutive tiles, the
+    // column tiles of a row block one after the other (A is read into one L2)
+    const int nb = gridDim.x, x = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+    const int t = x * per + min(x, rem) + blockIdx.x / 8;
+    const int m0 = (t / gx) * BM, n0 = (t % gx) * BN;
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    const int wm = (w / (BN / WN)) * WM, wn = (w % (BN / WN)) * WN;
+    f32x4 acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    u16x8 va[NVA], vb[NVB];
+    load_tile<BM, NT, AVK>(g.A, g.a_m, g.a_k, m0, g.M, 0, g.K, tid, va);
+    load_tile<BN, NT, BVK>(g.B, g.b_n, g.b_k, n0, g.N, 0, g.K, tid, vb);
+    const int nk = (g.K + GK - 1) / GK;
+    for (int it = 0; it < nk; ++it) {
+        bf16 *const as = As[it & 1], *const bs = Bs[it & 1];
+        store_tile<BM, NT, AVK>(as, tid, va);
+        store_tile<BN, NT, BVK>(bs, tid, vb);
+        __syncthreads();
+        const int k0 = it * GK;
+        if (it + 1 < nk) {  // the next chunk's loads in flight during this chunk's MFMAs
+            load_tile<BM, NT, AVK>(g.A, g.a_m, g.a_k, m0, g.M, k0 + GK, g.K, tid, va);
+            load_tile<BN, NT, BVK>(g.B, g.b_n, g.b_k, n0, g.N, k0 + GK, g.K, tid, vb);
+        }
+#pragma unroll
+        for (int ks = 0; ks < GK; ks += 32) {
+            if (k0 + ks >= g.K) break;  // no all-zero block beyond K
+            bf16x8 a[TI], b[TJ];
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+                a[i] = *(const bf16x8 *)&as[lds_piece(wm + 16 * i + (l & 15), (ks >> 3) + (l >> 4))];
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+                b[j] = *(const bf16x8 *)&bs[lds_piece(wn + 16 * j + (l & 15), (ks >> 3) + (l >> 4))];
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+        }
+        // (the buffer written at iteration it + 2 is read here: the barrier of iteration it + 1
+        // separates the two)
+    }
+    // transposed D of one MFMA: lane l, element v -> row l % 16, column 4 (l / 16) + v
+    const bool vec = g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        const int m = m0 + wm + 16 * i + (l & 15);
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            const int n = n0 + wn + 16 * j + 4 * (l >> 4);
+            f32x4 y = acc[i][j];
+            if (g.bias)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n + v < g.N) y[v] += g.bias[n + v];
+            float *c = g.C + (long long)m * g.ldc + n;
+            if (vec && n + 4 <= g.N) {
+                *(f32x4 *)c = y;
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n + v < g.N) c[v] = y[v];
+            }
+        }
+    }
+}
+
 // Up to three independent products in one launch: blocks [first[p], first[p + 1]) are
 // product p's grid gx[p] x gy[p] x gz[p] (x fastest), each block as k_gemm_bf16's.
 struct GemmGroup {
     GemmArgs g[3];
     int gx[3], gy[3], gz[3];
     int first[4];
+    int *step;          // in a combined training step: the Adam step count, advanced here (the
+    float *bias_corr;   // draw before reads the old one), and 1 - beta^t for both moments
+    float beta1, beta2;
 };
 __global__ void __launch_bounds__(256) k_gemm_bf16_group(GemmGroup gg) {
     const int bid = blockIdx.x;
+    if (gg.step && bid == 0 && threadIdx.x == 0) {
+        const int t = *gg.step + 1;
+        *gg.step = t;
+        gg.bias_corr[0] = 1.0f - powf(gg.beta1, (float)t);
+        gg.bias_corr[1] = 1.0f - powf(gg.beta2, (float)t);
+    }
     const int p = bid < gg.first[1] ? 0 : bid < gg.first[2] ? 1 : 2;
     const int q = bid - gg.first[p], gx = gg.gx[p], gy = gg.gy[p];
     gemm_tile(gg.g[p], q % gx, (q / gx) % gy, q / (gx * gy), gg.gz[p]);
@@ -255,13 +393,6 @@ __global__ void k_unblock(const bf16 *src, int C, int B, bf16 *dst) {
     dst[e] = src[((long long)(b >> 4) * C + c) * 16 + (b & 15)];
 }
 
-__global__ void k_to_bf16_rows(const float *X, int B, int din, int ldx, bf16 *Y, int ldy) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = e / ldy, c = e % ldy;
-    if (b >= B) return;
-    Y[(long long)b * ldy + c] = (c < din) ? (bf16)X[(long long)b * ldx + c] : (bf16)0.0f;
-}
-
 // Philox4x32-10 (Salmon et al., SC'11: two 32 x 32 -> 64-bit products per round, Weyl key
 // schedule): the counter-based generator of the minibatch draw
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
@@ -272,21 +403,6 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
         k1 += 0xBB67AE85u;
     }
     return c;
-}
-
-// Minibatch row b: data row i = floor(r M / 2^32), r the first Philox word at counter
-// (b, t, 0, 0), t the Adam steps taken (read on the device); its features as BF16 operands
-// [b][64] (zero padding) and its targets [b][N][2].  One block of 128 threads per row.
-__global__ void k_gather_sampled(const float *X_all, const float *U_all, long long M, int N, uint32_t k0,
-                                 uint32_t k1, const int *t, bf16 *Xb, float *Ub, int *idx) {
-    const int b = blockIdx.x;
-    const uint4 r = philox4x32_10(make_uint4((uint32_t)b, (uint32_t)*t, 0u, 0u), k0, k1);
-    const long long i = (long long)(((unsigned long long)r.x * (unsigned long long)M) >> 32);
-    if (threadIdx.x == 0) idx[b] = (int)i;
-    if (threadIdx.x < D_INP)
-        Xb[(long long)b * D_INP + threadIdx.x] =
-            threadIdx.x < D_IN ? (bf16)X_all[i * D_IN + threadIdx.x] : (bf16)0.0f;
-    for (int e = threadIdx.x; e < 2 * N; e += blockDim.x) Ub[(long long)b * 2 * N + e] = U_all[i * 2 * N + e];
 }
 
 // packed float32 weights -> BF16 GEMM operands (W3 padded to 256 columns)
@@ -351,17 +467,12 @@ __device__ __forceinline__ f32x4 mfma_frags(const bf16 *A, int lda, const bf16x8
 // Gaussian negative log-likelihood of target u for step t < 64, channel c (0 acceleration,
 // 1 steering) of one row whose outputs are o[256] (mean over B rows; constant 0.5 log 2 pi
 // dropped; steps t >= N do not enter, u unused): its term is returned, its gradient w.r.t.
-// the outputs written as BF16 to g[4 t + c] (mean) and g[4 t + 2 + c] (log scale), and,
-// when gt is not NULL, also to gt[(4 t + c) ldt] and gt[(4 t + 2 + c) ldt].
+// the outputs written as BF16 to g[4 t + c] (mean) and g[4 t + 2 + c] (log scale).
 __device__ __forceinline__ float nll_term(const float *o, float u, int t, int c, int N, float sig_a, float sig_d,
-                                          int B, bf16 *g, bf16 *gt = nullptr, long long ldt = 0) {
+                                          int B, bf16 *g) {
     if (t >= N) {
         g[4 * t + c] = (bf16)0.0f;
         g[4 * t + 2 + c] = (bf16)0.0f;
-        if (gt) {
-            gt[(4 * t + c) * ldt] = (bf16)0.0f;
-            gt[(4 * t + 2 + c) * ldt] = (bf16)0.0f;
-        }
         return 0.0f;
     }
     const float scale = c ? D_SCALE : A_SCALE;
@@ -372,56 +483,50 @@ __device__ __forceinline__ float nll_term(const float *o, float u, int t, int c,
     const float ls = lsp + cl;
     const float inv_s2 = expf(-2.0f * ls);
     const float res = u - mu;
-    const bf16 gm = (bf16)(-scale * res * inv_s2 / (float)B);
-    const bf16 gs = (bf16)((raw > LS_MIN && raw < LS_MAX) ? (1.0f - res * res * inv_s2) / (float)B : 0.0f);
-    g[4 * t + c] = gm;
-    g[4 * t + 2 + c] = gs;
-    if (gt) {
-        gt[(4 * t + c) * ldt] = gm;
-        gt[(4 * t + 2 + c) * ldt] = gs;
-    }
+    g[4 * t + c] = (bf16)(-scale * res * inv_s2 / (float)B);
+    g[4 * t + 2 + c] = (bf16)((raw > LS_MIN && raw < LS_MAX) ? (1.0f - res * res * inv_s2) / (float)B : 0.0f);
     return 0.5f * res * res * inv_s2 + ls;
 }
 
-// What a training forward also does: where its rows come from (row b of X and U, or, with
-// M > 0, a data-set row drawn as k_gather_sampled draws it, recorded in idx), the rows'
-// BF16 operands it leaves for the backward pass, and the loss gradient it ends with.
+// A training step's rows: row b of X and U or, with M > 0, data-set row floor(r M / 2^32), r
+// the first Philox word at counter (b, t, 0, 0), t the Adam steps taken (read on the device),
+// recorded in idx; and what the step leaves for the weight gradients.
 struct TrainIn {
     const float *U;  // targets [.][N][2], rows indexed like the features
     long long M;     // data-set rows when the minibatch is drawn, else 0
     uint32_t k0, k1;
     const int *t;    // Adam steps taken (the draw's counter)
     int *idx;        // [B] drawn rows
-    bf16 *Xb;        // [B][64] BF16 features (zero padding)
     int N;
     float sig_a, sig_d;
-    bf16 *dout;       // [B][256] loss gradient w.r.t. the outputs
-    float *loss_part; // [2 B] loss partials: row b steps 0-31 at 2 b, steps 32-63 at 2 b + 1
+    const bf16 *W3, *W2;  // weights as the input gradients read them ([fan_in][fan_out])
+    float *loss_part;     // [2 B] loss partials: row b steps 0-31 at 2 b, steps 32-63 at 2 b + 1
     // row-blocked copies [B / 16][columns][16] of the features, both hidden activations and
-    // the output gradient
-    bf16 *XB, *H1B, *H2B, *DB;
+    // the gradients w.r.t. the outputs and both pre-activations
+    bf16 *XB, *H1B, *H2B, *DB, *D2B, *D1B;
 };
 
 // Fused forward of 16 rows per workgroup: the three layers run back to back with the
-// hidden activations in LDS (BF16, as the tiled path stores them).  TRAIN: the rows are
-// fetched (drawn or not) from X, their BF16 operands written to Xb; the pre-activations
-// (float32) and activations (BF16) of both hidden layers are also written out ([B][256]
-// each), as the tiled products write them for the backward pass; and the loss and its
-// gradient are taken from the output tile, as k_nll takes them (same lane -> (step,
-// channel) map, same per-wave sums).
+// hidden activations in LDS (BF16 operands, float32 accumulation).  TRAIN goes on with the
+// loss, its gradient w.r.t. the outputs and the input gradients of layers 3 and 2 -- D2 =
+// BF16((D W3^T) GELU'(pre2)), D1 = BF16((D2 W2^T) GELU'(pre1)) -- for the same rows: the
+// pre-activations stay in the registers of the lane that formed them and D in LDS.  What the
+// weight gradients read (X, H1, H2, D, D2, D1) is written once, row-blocked.  Latency bound
+// (one workgroup per CU at 4096 rows): forward and input gradients as two launches, with the
+// pre-activations and D through memory, took 19 + 12 us there, this one 23.
 template <bool TRAIN>
 __global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_fwd16(const float *X, int ldx, int B, const bf16 *W1T,
                                                              const bf16 *W2T, const bf16 *W3T, const float *b1,
                                                              const float *b2, const float *b3, float *out, int ldo,
-                                                             int n_out, float *pre1, bf16 *h1o, float *pre2,
-                                                             bf16 *h2o, TrainIn ti) {
+                                                             int n_out, TrainIn ti) {
     static_assert(FWD_WAVES == 16, "one 16-column tile per wave and layer");
     constexpr int LX = D_INP + 8, LH = D_H + 8, LO = D_OUTP + 4;  // padded rows
     __shared__ __align__(16) bf16 xs[16 * LX];
     __shared__ __align__(16) bf16 h1[16 * LH];
     __shared__ __align__(16) bf16 h2[16 * LH];
     __shared__ float os[TRAIN ? 16 * LO : 1];
-    __shared__ __align__(16) bf16 dsb[TRAIN ? 16 * D_OUTP : 8];  // output gradient, row-blocked
+    __shared__ __align__(16) bf16 ds[TRAIN ? 16 * LH : 8];   // output gradient
+    __shared__ __align__(16) bf16 d2s[TRAIN ? 16 * LH : 8];
     __shared__ long long src[16];
     const int r0 = blockIdx.x * 16, tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int n0 = 16 * w, col = n0 + (l & 15);  // this wave's output columns in every layer
@@ -446,9 +551,7 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_fwd16(const float *X, in
     __syncthreads();
     for (int e = tid; e < 16 * D_INP; e += 64 * FWD_WAVES) {
         const int r = e / D_INP, c = e % D_INP;
-        const bf16 v = (r0 + r < B && c < D_IN) ? (bf16)X[src[r] * ldx + c] : (bf16)0.0f;
-        xs[r * LX + c] = v;
-        if (TRAIN && ti.Xb && r0 + r < B) ti.Xb[(long long)(r0 + r) * D_INP + c] = v;
+        xs[r * LX + c] = (r0 + r < B && c < D_IN) ? (bf16)X[src[r] * ldx + c] : (bf16)0.0f;
     }
     // the targets the loss section below takes (its pairs (row, step, channel) of both of
     // the wave's groups), fetched now
@@ -465,38 +568,28 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_fwd16(const float *X, in
     if (TRAIN)  // the rows' features into their row-blocked copy, 16 rows of a column contiguous
         for (int e = tid; e < 16 * D_INP; e += 64 * FWD_WAVES)
             ti.XB[(long long)r0 * D_INP + e] = xs[(e & 15) * LX + (e >> 4)];
+    float q1[4], q2[4];  // pre-activations of the lane's elements
     {  // layer 1
         const f32x4 acc = mfma_frags<D_INP>(xs, LX, f1, l);
         bf16 hb[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = 4 * (l >> 4) + v;
-            const float x = acc[v] + c1;
-            const bf16 h = (bf16)gelu_f(x);
-            hb[v] = h;
-            h1[row * LH + col] = h;
-            if (TRAIN && r0 + row < B) {
-                pre1[(long long)(r0 + row) * D_H + col] = x;
-                if (h1o) h1o[(long long)(r0 + row) * D_H + col] = h;
-            }
+            q1[v] = acc[v] + c1;
+            hb[v] = (bf16)gelu_f(q1[v]);
+            h1[(4 * (l >> 4) + v) * LH + col] = hb[v];
         }
         if (TRAIN) store_rows4(ti.H1B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
     }
     __syncthreads();
     {  // layer 2
         const f32x4 acc = mfma_frags<D_H>(h1, LH, f2, l);
+        if (TRAIN) load_frags<D_OUTP>(ti.W3, n0, l, f2);  // (the input gradient's fragments)
         bf16 hb[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = 4 * (l >> 4) + v;
-            const float x = acc[v] + c2;
-            const bf16 h = (bf16)gelu_f(x);
-            hb[v] = h;
-            h2[row * LH + col] = h;
-            if (TRAIN && r0 + row < B) {
-                pre2[(long long)(r0 + row) * D_H + col] = x;
-                if (h2o) h2o[(long long)(r0 + row) * D_H + col] = h;
-            }
+            q2[v] = acc[v] + c2;
+            hb[v] = (bf16)gelu_f(q2[v]);
+            h2[(4 * (l >> 4) + v) * LH + col] = hb[v];
         }
         if (TRAIN) store_rows4(ti.H2B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
     }
@@ -511,108 +604,179 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_fwd16(const float *X, in
             if (r0 + row < B && col < n_out) out[(long long)(r0 + row) * ldo + col] = o;
         }
     }
-    if (TRAIN) {
+    if constexpr (TRAIN) {
+        load_frags<D_H>(ti.W2, n0, l, f3);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {  // GELU' of the pre-activations
+            q1[v] = gelu_grad_f(q1[v]);
+            q2[v] = gelu_grad_f(q2[v]);
+        }
         __syncthreads();
         // 32 groups of 64 (step, channel) pairs: row vg / 2, steps 32 (vg & 1) + 0..31; wave
         // w takes groups w and w + 16 (rows w / 2 and w / 2 + 8)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int vg = w + 16 * j, row = vg >> 1, b = r0 + row;
-            if (b >= B) break;
-            float contrib = nll_term(os + row * LO, u[j], tt, cc, ti.N, ti.sig_a, ti.sig_d, B,
-                                     ti.dout + (long long)b * D_OUTP, dsb + row, 16);
+            if (b >= B) {  // (no such row: no gradient)
+                *(unsigned *)&ds[row * LH + 128 * (w & 1) + 2 * l] = 0u;
+                continue;
+            }
+            float contrib = nll_term(os + row * LO, u[j], tt, cc, ti.N, ti.sig_a, ti.sig_d, B, ds + row * LH);
             for (int off = 32; off > 0; off >>= 1) contrib += __shfl_xor(contrib, off);
             if (l == 0) ti.loss_part[2 * b + (vg & 1)] = contrib;
         }
         __syncthreads();
         // the output gradient's row-blocked copy: the block's 16 x 256 tile, contiguous
-        for (int e = tid; e < 16 * D_OUTP / 8; e += 64 * FWD_WAVES)
-            *(u16x8 *)&ti.DB[(long long)r0 * D_OUTP + 8 * e] = *(const u16x8 *)&dsb[8 * e];
-    }
-}
-
-// The same loss and gradient from outputs in memory (the tiled path), targets U[B][N][2].
-// One thread per (row, step < 64, channel); one partial per wave, summed in order by
-// k_grad_finish.
-__global__ void k_nll(const float *out, int ldo, const float *U, int B, int N, float sig_a, float sig_d, bf16 *dout,
-                      int ldd, float *loss_part) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = e >> 7, t = (e >> 1) & 63, c = e & 1;
-    float contrib = 0.0f;
-    if (b < B && 4 * t < ldd)
-        contrib = nll_term(out + (long long)b * ldo, t < N ? U[((long long)b * N + t) * 2 + c] : 0.0f, t, c, N, sig_a,
-                           sig_d, B, dout + (long long)b * ldd);
-    for (int off = 32; off > 0; off >>= 1) contrib += __shfl_xor(contrib, off);
-    if ((threadIdx.x & 63) == 0) loss_part[e >> 6] = contrib;
-}
-
-// Fused input gradients of 16 rows per workgroup, the backward counterpart of k_mlp_fwd16:
-// D2 = BF16((D W3^T) GELU'(pre2)), kept in LDS, then D1 = BF16((D2 W2^T) GELU'(pre1));
-// both written out for the weight gradients.  Same lane -> (row, k) map and k order as the
-// tiled products, so the same bits.
-__global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_bwd16(const bf16 *D, const bf16 *W3, const bf16 *W2,
-                                                             const float *pre2, const float *pre1, int B, bf16 *D2,
-                                                             bf16 *D1, bf16 *D2B, bf16 *D1B, int *step_count) {
-    static_assert(FWD_WAVES == 16, "one 16-column tile per wave and layer");
-    constexpr int LH = D_H + 8;
-    __shared__ __align__(16) bf16 ds[16 * LH];
-    __shared__ __align__(16) bf16 d2s[16 * LH];
-    const int r0 = blockIdx.x * 16, tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-    const int n0 = 16 * w, col = n0 + (l & 15);
-    // in a combined training step, the Adam step count advances here: the forward before
-    // has drawn its rows with the old count, the Adam step after reads the new one
-    if (step_count && blockIdx.x == 0 && tid == 0) *step_count += 1;
-    // everything that does not depend on the products first: the wave's weight fragments
-    // and GELU'(pre-activation) of its 4 x 2 elements (rows past B read row B - 1, unused)
-    bf16x8 f3[D_OUTP / 32], f2[D_H / 32];
-    load_frags<D_OUTP>(W3, n0, l, f3);
-    load_frags<D_H>(W2, n0, l, f2);
-    float q2[4], q1[4];
+        for (int e = tid; e < 16 * D_OUTP / 8; e += 64 * FWD_WAVES) {
+            u16x8 v;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const long long o = (long long)min(r0 + 4 * (l >> 4) + v, B - 1) * D_H + col;
-        q2[v] = pre2[o];
-        q1[v] = pre1[o];
-    }
-    for (int e = tid; e < 16 * (D_OUTP / 8); e += 64 * FWD_WAVES) {  // 16-byte vectors of 8 columns
-        const int r = e / (D_OUTP / 8), c = 8 * (e % (D_OUTP / 8));
-        u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (r0 + r < B) v = *(const u16x8 *)&D[(long long)(r0 + r) * D_OUTP + c];
-        *(u16x8 *)&ds[r * LH + c] = v;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        q2[v] = gelu_grad_f(q2[v]);
-        q1[v] = gelu_grad_f(q1[v]);
-    }
-    __syncthreads();
-    {  // D2
-        const f32x4 acc = mfma_frags<D_OUTP>(ds, LH, f3, l);
+            for (int j = 0; j < 8; ++j) v[j] = __builtin_bit_cast(unsigned short, ds[(8 * (e & 1) + j) * LH + (e >> 1)]);
+            *(u16x8 *)&ti.DB[(long long)r0 * D_OUTP + 8 * e] = v;
+        }
         bf16 hb[4];
+        {  // D2
+            const f32x4 acc = mfma_frags<D_OUTP>(ds, LH, f2, l);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = 4 * (l >> 4) + v;
-            bf16 h = (bf16)0.0f;
-            if (r0 + row < B) {
-                h = (bf16)(acc[v] * q2[v]);
-                if (D2) D2[(long long)(r0 + row) * D_H + col] = h;
+            for (int v = 0; v < 4; ++v) {
+                const int row = 4 * (l >> 4) + v;
+                hb[v] = r0 + row < B ? (bf16)(acc[v] * q2[v]) : (bf16)0.0f;
+                d2s[row * LH + col] = hb[v];
             }
-            hb[v] = h;
-            d2s[row * LH + col] = h;
+            store_rows4(ti.D2B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
         }
-        store_rows4(D2B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
+        __syncthreads();
+        {  // D1
+            const f32x4 acc = mfma_frags<D_H>(d2s, LH, f3, l);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) hb[v] = (bf16)(acc[v] * q1[v]);
+            store_rows4(ti.D1B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
+        }
     }
-    __syncthreads();
-    {  // D1
-        const f32x4 acc = mfma_frags<D_H>(d2s, LH, f2, l);
-        bf16 hb[4];
+}
+
+// Forward of a large batch: persistent workgroups of eight waves, 16 RT rows at a time.  Every
+// wave owns 32 columns of all three layers and keeps their weight fragments (144 registers)
+// for the whole batch; the rows' activations pass through LDS (32 16-byte pieces per row,
+// permuted by the row).  The products are formed transposed, so that a lane holds four
+// consecutive columns of a row: 8-byte LDS and 16-byte global stores.  Same lane -> k map and
+// k order as k_mlp_fwd16, so the same bits.  Bound by the GELUs (two tanh per weight column
+// and row, about 40 instructions each) and the output's 52 MB: 65536 rows take 61 us (three
+// tiled products and a conversion: 231).
+constexpr int FWD_WIDE_WAVES = 8;
+__device__ __forceinline__ int act_piece(int row, int c) { return row * D_H + 8 * (c ^ (row & 15)); }
+
+template <int RT>
+__global__ void __launch_bounds__(64 * FWD_WIDE_WAVES) k_mlp_fwd_wide(const float *X, int B, const bf16 *W1T,
+                                                                     const bf16 *W2T, const bf16 *W3T, const float *b1,
+                                                                     const float *b2, const float *b3, float *out,
+                                                                     int ldo) {
+    constexpr int R = 16 * RT, NT = 64 * FWD_WIDE_WAVES, NX = (R * D_IN + NT - 1) / NT;
+    __shared__ __align__(16) bf16 xs[R * D_INP];
+    __shared__ __align__(16) bf16 h1[R * D_H];
+    __shared__ __align__(16) bf16 h2[R * D_H];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lr = l & 15, lk = l >> 4;
+    const int n0 = 32 * w;
+    bf16x8 f1[2][D_INP / 32], f2[2][D_H / 32], f3[2][D_H / 32];
+    f32x4 c1[2], c2[2], c3[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        load_frags<D_INP>(W1T, n0 + 16 * j, l, f1[j]);
+        load_frags<D_H>(W2T, n0 + 16 * j, l, f2[j]);
+        load_frags<D_H>(W3T, n0 + 16 * j, l, f3[j]);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = 4 * (l >> 4) + v;
-            hb[v] = (bf16)(acc[v] * q1[v]);
-            if (D1 && r0 + row < B) D1[(long long)(r0 + row) * D_H + col] = hb[v];
+            const int n = n0 + 16 * j + 4 * lk + v;
+            c1[j][v] = b1[n];
+            c2[j][v] = b2[n];
+            c3[j][v] = n < D_OUT ? b3[n] : 0.0f;
         }
-        store_rows4(D1B + (long long)r0 * D_H + col * 16 + 4 * (l >> 4), hb);
+    }
+    const int tiles = (B + R - 1) / R;
+    const bool vec = ldo % 4 == 0 && ((uintptr_t)out & 15) == 0;
+    float x[NX];
+    auto fetch = [&](int t) {
+        const long long o = (long long)t * R * D_IN, end = (long long)B * D_IN;
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int e = tid + NT * q;
+            x[q] = e < R * D_IN && o + e < end ? X[o + e] : 0.0f;
+        }
+    };
+    auto hidden = [&](f32x4 acc, f32x4 c, bf16 *h, int row, int n) {
+        ushort4 u;
+        u.x = __builtin_bit_cast(unsigned short, (bf16)gelu_f(acc[0] + c[0]));
+        u.y = __builtin_bit_cast(unsigned short, (bf16)gelu_f(acc[1] + c[1]));
+        u.z = __builtin_bit_cast(unsigned short, (bf16)gelu_f(acc[2] + c[2]));
+        u.w = __builtin_bit_cast(unsigned short, (bf16)gelu_f(acc[3] + c[3]));
+        *(ushort4 *)&h[act_piece(row, n >> 3) + (n & 7)] = u;
+    };
+    for (int e = tid; e < R * (D_INP - D_IN); e += NT) {  // the padding columns stay zero
+        const int r = e / (D_INP - D_IN), c = D_IN + e % (D_INP - D_IN);
+        xs[lds_piece(r, c >> 3) + (c & 7)] = (bf16)0.0f;
+    }
+    if ((int)blockIdx.x < tiles) fetch(blockIdx.x);
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int e = tid + NT * q, r = e / D_IN, c = e % D_IN;
+            if (e < R * D_IN) xs[lds_piece(r, c >> 3) + (c & 7)] = (bf16)x[q];
+        }
+        __syncthreads();
+        if (t + (int)gridDim.x < tiles) fetch(t + gridDim.x);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {  // layer 1
+            f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+            for (int q = 0; q < D_INP / 32; ++q) {
+                const bf16x8 a = *(const bf16x8 *)&xs[lds_piece(16 * i + lr, 4 * q + lk)];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[j][q], a, acc[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) hidden(acc[j], c1[j], h1, 16 * i + lr, n0 + 16 * j + 4 * lk);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {  // layer 2
+            f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+            for (int q = 0; q < D_H / 32; ++q) {
+                const bf16x8 a = *(const bf16x8 *)&h1[act_piece(16 * i + lr, 4 * q + lk)];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f2[j][q], a, acc[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) hidden(acc[j], c2[j], h2, 16 * i + lr, n0 + 16 * j + 4 * lk);
+        }
+        __syncthreads();
+        if (n0 < D_OUT) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {  // layer 3
+                f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+                for (int q = 0; q < D_H / 32; ++q) {
+                    const bf16x8 a = *(const bf16x8 *)&h2[act_piece(16 * i + lr, 4 * q + lk)];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f3[j][q], a, acc[j], 0, 0, 0);
+                }
+                const long long row = (long long)t * R + 16 * i + lr;
+                if (row >= B) continue;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int n = n0 + 16 * j + 4 * lk;
+                    if (n >= D_OUT) continue;
+                    const f32x4 y = acc[j] + c3[j];
+                    float *o = out + row * ldo + n;
+                    if (vec) *(f32x4 *)o = y;
+                    else
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) o[v] = y[v];
+                }
+            }
+        }
+        // (the next rows' features are written to xs two barriers after layer 1 read it, its
+        // layer 1 writes h1 one barrier after layer 2 read it, layer 2 h2 two after layer 3)
     }
 }
 
@@ -664,14 +828,21 @@ __device__ __forceinline__ void write_copies(const Bf16Copies &w, size_t e, floa
 struct AdamArgs {
     float *P, *m, *v;
     float lr, b1, b2, eps;
-    const int *t_prev;
+    const int *t_prev;       // step number t = *t_prev + 1
     Bf16Copies copies;
-    int t_add;  // step number t = *t_prev + t_add (0 when the count was already advanced)
+    const float *bias_corr;  // 1 - beta^t formed before (two powf per parameter saved), or NULL
 };
 // Adam on parameter e with gradient g (bias-corrected moments, step t)
 __device__ __forceinline__ void adam_update(const AdamArgs &a, size_t e, float g) {
-    const float t = (float)(*a.t_prev + a.t_add);
-    const float bc1 = 1.0f - powf(a.b1, t), bc2 = 1.0f - powf(a.b2, t);
+    float bc1, bc2;
+    if (a.bias_corr) {
+        bc1 = a.bias_corr[0];
+        bc2 = a.bias_corr[1];
+    } else {
+        const float t = (float)(*a.t_prev + 1);
+        bc1 = 1.0f - powf(a.b1, t);
+        bc2 = 1.0f - powf(a.b2, t);
+    }
     const float mm = a.b1 * a.m[e] + (1.0f - a.b1) * g;
     const float vv = a.b2 * a.v[e] + (1.0f - a.b2) * g * g;
     a.m[e] = mm;
@@ -751,12 +922,11 @@ struct sgtp_mlp {
     bf16 *W1 = nullptr, *W2 = nullptr, *W3 = nullptr;              // BF16 operands
     bf16 *W1T = nullptr, *W2T = nullptr, *W3T = nullptr;           // transposed (fused forward)
     float *b3p = nullptr;
-    bf16 *X = nullptr, *H1 = nullptr, *H2 = nullptr, *D = nullptr, *D2 = nullptr, *D1 = nullptr;
-    float *PRE1 = nullptr, *PRE2 = nullptr, *OUT = nullptr, *loss = nullptr;
+    float *OUT = nullptr, *loss = nullptr;
+    float *bias_corr = nullptr;  // 1 - beta^t of the current combined training step [2]
     float *PART = nullptr;  // split-K partial products of the weight and bias gradients [3][64][257][256]
     float *LP = nullptr;    // per-wave loss partials [2 B_max + 4]
     int *adam_t = nullptr;  // device: Adam steps taken
-    float *UB = nullptr;    // gathered targets of a sampled gradient [B_max][N_H][2]
     int *IDX = nullptr;     // rows drawn by the last sampled gradient [B_max]
     // row-blocked copies [B / 16][columns][16] of X, H1, H2, D, D2 and D1, written by the
     // fused kernels (one contiguous block per workgroup) so the weight-gradient products
@@ -764,7 +934,6 @@ struct sgtp_mlp {
     bf16 *XB = nullptr, *H1B = nullptr, *H2B = nullptr, *DB = nullptr, *D2B = nullptr, *D1B = nullptr;
     int last_B = 0;  // rows of the last sgtp_mlp_grad (its workspace tensors stay until the next call)
     bool last_sampled = false;  // the last gradient drew its rows on the device
-    bool last_blocked = false;  // the last gradient left H1, H2, D2 and D1 only row-blocked
 };
 
 namespace {
@@ -801,12 +970,31 @@ int stage_mode(const void *P, long long s_r, long long s_k) {
     return STAGE_ELEM;
 }
 
-// H output: BF16 GELU(C), or with gpre BF16 C x GELU'(gpre) (an activation gradient)
+template <int BM, int BN, int WM, int WN>
+void launch_big(hipStream_t st, const GemmArgs &g, bool ak, bool bk) {
+    const int gx = (g.N + BN - 1) / BN;
+    const dim3 grid((unsigned)((long long)gx * ((g.M + BM - 1) / BM))), block(64 * (BM / WM) * (BN / WN));
+    if (ak && bk) hipLaunchKernelGGL((k_gemm_big<BM, BN, WM, WN, true, true>), grid, block, 0, st, g, gx);
+    else if (ak) hipLaunchKernelGGL((k_gemm_big<BM, BN, WM, WN, true, false>), grid, block, 0, st, g, gx);
+    else if (bk) hipLaunchKernelGGL((k_gemm_big<BM, BN, WM, WN, false, true>), grid, block, 0, st, g, gx);
+    else hipLaunchKernelGGL((k_gemm_big<BM, BN, WM, WN, false, false>), grid, block, 0, st, g, gx);
+}
+
 void gemm(hipStream_t st, const bf16 *A, long long a_m, long long a_k, const bf16 *B, long long b_k, long long b_n,
-          int M, int N, int K, const float *bias, float *C, long long ldc, bf16 *H, long long ldh,
-          const float *gpre = nullptr) {
-    GemmArgs g{A, a_m, a_k, B, b_k, b_n, M, N, K, bias, C, ldc, 0, H, ldh, gpre,
+          int M, int N, int K, const float *bias, float *C, long long ldc) {
+    GemmArgs g{A, a_m, a_k, B, b_k, b_n, M, N, K, bias, C, ldc, 0,
                stage_mode(A, a_m, a_k), stage_mode(B, b_n, b_k), -1};
+    // Large tiles wherever each operand has a unit stride (any alignment).  256 x 256 where
+    // those tiles fill the CUs (their MFMAs per LDS byte are twice the smaller ones': 16384 x
+    // 1024 x 1024 51 us against 67), 128 x 128 otherwise (2048^3 34 against 76, 8192 x 512 x
+    // 512 14 against 28).  The 64 x 64 kernel took 199, 116 and 35 us for these.
+    const bool ak = a_k == 1, bk = b_k == 1;
+    if ((ak || a_m == 1) && (bk || b_n == 1)) {
+        const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
+        if (t256 >= 224 && t256 * 4 >= (t256 + 255) / 256 * 256 * 3) launch_big<256, 256, 128, 64>(st, g, ak, bk);
+        else launch_big<128, 128, 32, 64>(st, g, ak, bk);
+        return;
+    }
     hipLaunchKernelGGL(k_gemm_bf16, dim3((N + 63) / 64, (M + 63) / 64, 1), dim3(256), 0, st, g);
 }
 
@@ -814,36 +1002,17 @@ void gemm(hipStream_t st, const bf16 *A, long long a_m, long long a_k, const bf1
 // column sums of B, as one product with an extra row of ones in A, K split into `splits`
 // slices: partial products into `part` [splits][M + 1][N]; the slices are summed in order
 // by k_grad_finish (its descriptor is returned).  The product becomes member p of the
-// group launch grp.  blk_mode STAGE_BLK16: both operands row-blocked (strides as that
-// mode reads them).
-SliceSum gemm_wgrad(GemmGroup &grp, int p, float *part, const bf16 *A, long long a_m, long long a_k, const bf16 *B,
-                    long long b_k, long long b_n, int M, int N, int K, float *dst, int ldd, float *bias_dst,
-                    int splits, int blk_mode = -1) {
+// group launch grp.  Both operands are row-blocked copies, of lda and ldb columns.
+SliceSum gemm_wgrad(GemmGroup &grp, int p, float *part, const bf16 *A, int lda, const bf16 *B, int ldb, int M, int N,
+                    int K, float *dst, float *bias_dst, int splits) {
     const int R = M + 1;  // row M of A reads as 1: the bias gradient
-    const int am = blk_mode >= 0 ? blk_mode : stage_mode(A, a_m, a_k);
-    const int bm = blk_mode >= 0 ? blk_mode : stage_mode(B, b_n, b_k);
-    grp.g[p] = GemmArgs{A, a_m, a_k, B, b_k, b_n, R, N, K, nullptr, part, N, (long long)R * N, nullptr, 0, nullptr,
-                        am, bm, M};
+    grp.g[p] = GemmArgs{A, 16, 16 * lda, B, 16 * ldb, 16, R, N, K, nullptr, part, N, (long long)R * N,
+                        STAGE_BLK16, STAGE_BLK16, M};
     grp.gx[p] = (N + 63) / 64;
     grp.gy[p] = (R + 63) / 64;
     grp.gz[p] = splits;
     grp.first[p + 1] = grp.first[p] + grp.gx[p] * grp.gy[p] * splits;
-    return SliceSum{part, (long long)R * N, splits, R, N, N, ldd, dst, bias_dst};
-}
-
-// forward of B rows (features float32 [B][ldx]) into out[B][ldo], n_out columns (200, or
-// 256 with the zero padding for the loss)
-// (products only: the BF16 operands are already in m->X)
-int forward_bf16(sgtp_mlp *m, int B, float *out, int ldo, int n_out, hipStream_t st) {
-    gemm(st, m->X, D_INP, 1, m->W1, D_H, 1, B, D_H, D_IN, m->P + P_B1, m->PRE1, D_H, m->H1, D_H);
-    gemm(st, m->H1, D_H, 1, m->W2, D_H, 1, B, D_H, D_H, m->P + P_B2, m->PRE2, D_H, m->H2, D_H);
-    gemm(st, m->H2, D_H, 1, m->W3, D_OUTP, 1, B, n_out, D_H, m->b3p, out, ldo, nullptr, 0);
-    MCHK(m, hipGetLastError());
-    return SGTP_OK;
-}
-int forward(sgtp_mlp *m, const float *X, int ldx, int B, float *out, int ldo, int n_out, hipStream_t st) {
-    hipLaunchKernelGGL(k_to_bf16_rows, dim3((B * D_INP + 255) / 256), dim3(256), 0, st, X, B, D_IN, ldx, m->X, D_INP);
-    return forward_bf16(m, B, out, ldo, n_out, st);
+    return SliceSum{part, (long long)R * N, splits, R, N, N, N, dst, bias_dst};
 }
 
 }  // namespace
@@ -873,19 +1042,11 @@ int sgtp_mlp_create(int B_max, sgtp_mlp **out) {
     al((void **)&m->W1T, (size_t)D_H * D_INP * 2);
     al((void **)&m->W2T, (size_t)D_H * D_H * 2);
     al((void **)&m->W3T, (size_t)D_H * D_H * 2);
-    al((void **)&m->X, (size_t)B_max * D_INP * 2);
-    al((void **)&m->H1, (size_t)B_max * D_H * 2);
-    al((void **)&m->H2, (size_t)B_max * D_H * 2);
-    al((void **)&m->D, (size_t)B_max * D_OUTP * 2);
-    al((void **)&m->D2, (size_t)B_max * D_H * 2);
-    al((void **)&m->D1, (size_t)B_max * D_H * 2);
-    al((void **)&m->PRE1, (size_t)B_max * D_H * 4);
-    al((void **)&m->PRE2, (size_t)B_max * D_H * 4);
     al((void **)&m->OUT, (size_t)B_max * D_OUTP * 4);
     al((void **)&m->PART, (size_t)3 * MAX_SPLITS * (D_H + 1) * D_OUTP * 4);
     al((void **)&m->LP, (size_t)(2 * B_max + 4) * 4);
     al((void **)&m->adam_t, 4);
-    al((void **)&m->UB, (size_t)B_max * N_H * 2 * 4);
+    al((void **)&m->bias_corr, 8);
     al((void **)&m->IDX, (size_t)B_max * 4);
     al((void **)&m->loss, 4);
     const size_t rows16 = (size_t)(B_max + 15) / 16 * 16;
@@ -906,9 +1067,8 @@ int sgtp_mlp_create(int B_max, sgtp_mlp **out) {
 int sgtp_mlp_destroy(sgtp_mlp *m) {
     if (!m) return SGTP_EINVAL;
     (void)hipDeviceSynchronize();
-    void *bufs[] = {m->P,  m->G,  m->Mm, m->Vv,   m->W1,   m->W2,  m->W3, m->b3p, m->X,    m->H1,   m->H2,
-                    m->D,  m->D1, m->PRE1, m->PRE2, m->OUT, m->PART, m->loss, m->W1T, m->W2T, m->W3T,
-                    m->D2, m->LP, m->adam_t, m->UB, m->IDX, m->XB, m->H1B, m->H2B, m->DB, m->D2B, m->D1B};
+    void *bufs[] = {m->P,   m->G,   m->Mm,   m->Vv,   m->W1,  m->W2,     m->W3,        m->b3p, m->W1T, m->W2T, m->W3T, m->OUT,
+                    m->PART, m->loss, m->LP, m->adam_t, m->IDX, m->XB, m->H1B, m->H2B, m->DB, m->D2B, m->D1B, m->bias_corr};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete m;
@@ -951,19 +1111,23 @@ int sgtp_mlp_forward(sgtp_mlp *m, const float *X, int B, float *out, int ld_out,
     if (B <= FUSED_MAX_ROWS) {  // planning-size batches: one fused kernel
         hipLaunchKernelGGL(k_mlp_fwd16<false>, dim3((B + 15) / 16), dim3(64 * FWD_WAVES), 0, st, X,
                            D_IN, B, m->W1T, m->W2T, m->W3T, m->P + P_B1, m->P + P_B2, m->P + P_B3, out, ld_out, D_OUT,
-                           nullptr, nullptr, nullptr, nullptr, TrainIn{});
+                           TrainIn{});
         MCHK(m, hipGetLastError());
         return SGTP_OK;
     }
-    return forward(m, X, D_IN, B, out, ld_out, D_OUT, st);
+    // larger batches: weights held in registers, 32 rows at a time until 64-row steps fill the CUs
+    const int cus = 256;
+    if (B < 64 * cus)
+        hipLaunchKernelGGL(k_mlp_fwd_wide<2>, dim3(std::min(cus, (B + 31) / 32)), dim3(64 * FWD_WIDE_WAVES), 0, st, X, B,
+                           m->W1T, m->W2T, m->W3T, m->P + P_B1, m->P + P_B2, m->P + P_B3, out, ld_out);
+    else
+        hipLaunchKernelGGL(k_mlp_fwd_wide<4>, dim3(cus), dim3(64 * FWD_WIDE_WAVES), 0, st, X, B, m->W1T, m->W2T, m->W3T,
+                           m->P + P_B1, m->P + P_B2, m->P + P_B3, out, ld_out);
+    MCHK(m, hipGetLastError());
+    return SGTP_OK;
 }
 
 namespace {
-// Training batches up to this many rows take the fused forward (one launch, the hidden
-// layers written out for the backward pass); larger ones the tiled products.  Both give
-// the same bits.
-constexpr int FUSED_TRAIN_MAX = 8192;
-
 // Where the B rows of a gradient come from: features X [.][50] and targets U [.][N][2],
 // row b of each, or (M > 0) rows drawn from a data set of M rows with Philox key (k0, k1)
 struct RowSrc {
@@ -975,72 +1139,35 @@ struct RowSrc {
 // Adam's arguments over the network's parameters and moments
 AdamArgs adam_args(sgtp_mlp *m, float lr, float beta1, float beta2, float eps) {
     const Bf16Copies copies{m->W1, m->W2, m->W3, m->W1T, m->W2T, m->W3T, m->b3p};
-    return AdamArgs{m->P, m->Mm, m->Vv, lr, beta1, beta2, eps, m->adam_t, copies, 1};
+    return AdamArgs{m->P, m->Mm, m->Vv, lr, beta1, beta2, eps, m->adam_t, copies, nullptr};
 }
 
 // The gradient of B rows into m->G (and the loss); with ad, each gradient value also takes
-// its Adam step inside the slice-sum launch, and *counted tells whether the step count was
-// advanced on the way (by the fused input-gradient kernel) or is the caller's to advance.
+// its Adam step inside the slice-sum launch and the step count is advanced on the way.
 int grad_rows(sgtp_mlp *m, const RowSrc &rs, int B, int N, float sig_a, float sig_d, float *loss, float *grads,
-              hipStream_t st, const AdamArgs *ad = nullptr, bool *counted = nullptr) {
-    if (counted) *counted = false;
-    int n_lp;
-    if (B <= FUSED_TRAIN_MAX) {  // fetch, forward and loss gradient in one launch
-        // the weight gradients read the row-blocked copies; the row layouts of the features,
-        // hidden activations and input gradients are not written (sgtp_mlp_workspace
-        // rebuilds them from the blocked copies)
-        const TrainIn ti{rs.U,  rs.M,  rs.k0, rs.k1, m->adam_t, m->IDX, nullptr, N,
-                         sig_a, sig_d, m->D,  m->LP, m->XB,  m->H1B,    m->H2B,  m->DB};
-        hipLaunchKernelGGL(k_mlp_fwd16<true>, dim3((B + 15) / 16), dim3(64 * FWD_WAVES), 0, st, rs.X,
-                           D_IN, B, m->W1T, m->W2T, m->W3T, m->P + P_B1, m->P + P_B2, m->b3p, m->OUT, D_OUTP, D_OUTP,
-                           m->PRE1, nullptr, m->PRE2, nullptr, ti);
-        n_lp = 2 * B;
-    } else {
-        const float *U = rs.U;
-        if (rs.M > 0) {
-            hipLaunchKernelGGL(k_gather_sampled, dim3(B), dim3(128), 0, st, rs.X, rs.U, rs.M, N, rs.k0, rs.k1,
-                               m->adam_t, m->X, m->UB, m->IDX);
-            U = m->UB;
-        } else {
-            hipLaunchKernelGGL(k_to_bf16_rows, dim3((B * D_INP + 255) / 256), dim3(256), 0, st, rs.X, B, D_IN, D_IN,
-                               m->X, D_INP);
-        }
-        int rc = forward_bf16(m, B, m->OUT, D_OUTP, D_OUTP, st);
-        if (rc) return rc;
-        const int nll_blocks = (B * 128 + 255) / 256;
-        hipLaunchKernelGGL(k_nll, dim3(nll_blocks), dim3(256), 0, st, m->OUT, D_OUTP, U, B, N, sig_a, sig_d, m->D,
-                           D_OUTP, m->LP);
-        n_lp = 4 * nll_blocks;
-    }
+              hipStream_t st, const AdamArgs *ad = nullptr) {
+    // rows, forward, loss gradient and input gradients in one launch
+    const TrainIn ti{rs.U,  rs.M,  rs.k0, rs.k1,  m->adam_t, m->IDX, N,      sig_a,
+                     sig_d, m->W3, m->W2, m->LP,  m->XB,     m->H1B, m->H2B, m->DB, m->D2B, m->D1B};
+    hipLaunchKernelGGL(k_mlp_fwd16<true>, dim3((B + 15) / 16), dim3(64 * FWD_WAVES), 0, st, rs.X, D_IN, B, m->W1T,
+                       m->W2T, m->W3T, m->P + P_B1, m->P + P_B2, m->b3p, m->OUT, D_OUTP, D_OUTP, ti);
+    const int n_lp = 2 * B;
     // partial products of the three weight-and-bias gradients go to separate thirds of PART
     const size_t third = (size_t)MAX_SPLITS * (D_H + 1) * D_OUTP;
-    if (B <= FUSED_TRAIN_MAX) {  // dH2 = D W3^T and dH1 = D2 W2^T in one launch
-        hipLaunchKernelGGL(k_mlp_bwd16, dim3((B + 15) / 16), dim3(64 * FWD_WAVES), 0, st, m->D, m->W3, m->W2,
-                           m->PRE2, m->PRE1, B, nullptr, nullptr, m->D2B, m->D1B, ad ? m->adam_t : nullptr);
-        if (counted) *counted = ad != nullptr;
-    } else {
-        gemm(st, m->D, D_OUTP, 1, m->W3, 1, D_OUTP, B, D_H, D_OUTP, nullptr, nullptr, 0, m->D2, D_H, m->PRE2);
-        gemm(st, m->D2, D_H, 1, m->W2, 1, D_H, B, D_H, D_H, nullptr, nullptr, 0, m->D1, D_H, m->PRE1);
-    }
     FinishArgs fa{};
     GemmGroup grp{};
-    // gW3 = H2^T D and gb3 = column sums of D (one product); gW2 = H1^T D2, gb2;
-    // gW1 = X^T D1, gb1.  After the fused kernels the operands are read from their
-    // row-blocked copies (same products, 16 consecutive k contiguous).
-    if (B <= FUSED_TRAIN_MAX) {
-        fa.s[0] = gemm_wgrad(grp, 0, m->PART, m->H2B, 16, 16 * D_H, m->DB, 16 * D_OUTP, 16, D_H, D_OUT, B,
-                             m->G + P_W3, D_OUT, m->G + P_B3, k_splits(D_H, D_OUT, B), STAGE_BLK16);
-        fa.s[1] = gemm_wgrad(grp, 1, m->PART + third, m->H1B, 16, 16 * D_H, m->D2B, 16 * D_H, 16, D_H, D_H, B,
-                             m->G + P_W2, D_H, m->G + P_B2, k_splits(D_H, D_H, B), STAGE_BLK16);
-        fa.s[2] = gemm_wgrad(grp, 2, m->PART + 2 * third, m->XB, 16, 16 * D_INP, m->D1B, 16 * D_H, 16, D_IN, D_H,
-                             B, m->G + P_W1, D_H, m->G + P_B1, k_splits(D_IN, D_H, B), STAGE_BLK16);
-    } else {
-        fa.s[0] = gemm_wgrad(grp, 0, m->PART, m->H2, 1, D_H, m->D, D_OUTP, 1, D_H, D_OUT, B, m->G + P_W3, D_OUT,
-                             m->G + P_B3, k_splits(D_H, D_OUT, B));
-        fa.s[1] = gemm_wgrad(grp, 1, m->PART + third, m->H1, 1, D_H, m->D2, D_H, 1, D_H, D_H, B, m->G + P_W2, D_H,
-                             m->G + P_B2, k_splits(D_H, D_H, B));
-        fa.s[2] = gemm_wgrad(grp, 2, m->PART + 2 * third, m->X, 1, D_INP, m->D1, D_H, 1, D_IN, D_H, B,
-                             m->G + P_W1, D_H, m->G + P_B1, k_splits(D_IN, D_H, B));
+    // gW3 = H2^T D and gb3 = column sums of D (one product); gW2 = H1^T D2, gb2; gW1 = X^T D1, gb1
+    fa.s[0] = gemm_wgrad(grp, 0, m->PART, m->H2B, D_H, m->DB, D_OUTP, D_H, D_OUT, B, m->G + P_W3, m->G + P_B3,
+                         k_splits(D_H, D_OUT, B));
+    fa.s[1] = gemm_wgrad(grp, 1, m->PART + third, m->H1B, D_H, m->D2B, D_H, D_H, D_H, B, m->G + P_W2, m->G + P_B2,
+                         k_splits(D_H, D_H, B));
+    fa.s[2] = gemm_wgrad(grp, 2, m->PART + 2 * third, m->XB, D_INP, m->D1B, D_H, D_IN, D_H, B, m->G + P_W1,
+                         m->G + P_B1, k_splits(D_IN, D_H, B));
+    if (ad) {
+        grp.step = m->adam_t;
+        grp.bias_corr = m->bias_corr;
+        grp.beta1 = ad->b1;
+        grp.beta2 = ad->b2;
     }
     hipLaunchKernelGGL(k_gemm_bf16_group, dim3(grp.first[3]), dim3(256), 0, st, grp);
     // the slice sums and the loss in one launch
@@ -1055,12 +1182,11 @@ int grad_rows(sgtp_mlp *m, const RowSrc &rs, int B, int N, float sig_a, float si
     fa.adam_on = ad != nullptr;
     if (ad) {
         fa.adam = *ad;
-        if (counted && *counted) fa.adam.t_add = 0;
+        fa.adam.bias_corr = m->bias_corr;
     }
     hipLaunchKernelGGL(k_grad_finish, dim3(fa.first[3] + 1), dim3(256), 0, st, fa);
     MCHK(m, hipGetLastError());
     m->last_B = B;
-    m->last_blocked = B <= FUSED_TRAIN_MAX;
     if (grads) MCHK(m, hipMemcpyAsync(grads, m->G, P_TOTAL * 4, hipMemcpyDeviceToDevice, st));
     return SGTP_OK;
 }
@@ -1094,33 +1220,27 @@ int sgtp_mlp_grad_sampled(sgtp_mlp *m, const float *X_all, const float *U_all, l
 int sgtp_mlp_workspace(sgtp_mlp *m, int which, void *dst, void *stream) {
     if (!m || !dst) return SGTP_EINVAL;
     if (m->last_B < 1) return mfail(m, SGTP_EINVAL, "no gradient computed yet");
-    const void *src = nullptr;
-    size_t row = 0;
-    if (m->last_blocked && (which == SGTP_MLP_WS_H1 || which == SGTP_MLP_WS_H2 || which == SGTP_MLP_WS_D2 ||
-                            which == SGTP_MLP_WS_D1)) {
-        const bf16 *blk = which == SGTP_MLP_WS_H1 ? m->H1B : which == SGTP_MLP_WS_H2 ? m->H2B
-                          : which == SGTP_MLP_WS_D2 ? m->D2B : m->D1B;
-        const long long n = (long long)m->last_B * D_H;
-        hipLaunchKernelGGL(k_unblock, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, blk, D_H,
-                           m->last_B, (bf16 *)dst);
-        MCHK(m, hipGetLastError());
-        return SGTP_OK;
-    }
+    hipStream_t st = (hipStream_t)stream;
+    const bf16 *blk = nullptr;
     switch (which) {
-        case SGTP_MLP_WS_H1: src = m->H1; row = D_H * 2; break;
-        case SGTP_MLP_WS_H2: src = m->H2; row = D_H * 2; break;
-        case SGTP_MLP_WS_OUT: src = m->OUT; row = D_OUTP * 4; break;
-        case SGTP_MLP_WS_D3: src = m->D; row = D_OUTP * 2; break;
-        case SGTP_MLP_WS_D2: src = m->D2; row = D_H * 2; break;
-        case SGTP_MLP_WS_D1: src = m->D1; row = D_H * 2; break;
+        case SGTP_MLP_WS_H1: blk = m->H1B; break;
+        case SGTP_MLP_WS_H2: blk = m->H2B; break;
+        case SGTP_MLP_WS_D3: blk = m->DB; break;
+        case SGTP_MLP_WS_D2: blk = m->D2B; break;
+        case SGTP_MLP_WS_D1: blk = m->D1B; break;
+        case SGTP_MLP_WS_OUT:
+            MCHK(m, hipMemcpyAsync(dst, m->OUT, (size_t)D_OUTP * 4 * m->last_B, hipMemcpyDeviceToDevice, st));
+            return SGTP_OK;
         case SGTP_MLP_WS_IDX:
             if (!m->last_sampled) return mfail(m, SGTP_EINVAL, "the last gradient did not draw its rows");
-            src = m->IDX;
-            row = 4;
-            break;
+            MCHK(m, hipMemcpyAsync(dst, m->IDX, (size_t)4 * m->last_B, hipMemcpyDeviceToDevice, st));
+            return SGTP_OK;
         default: return mfail(m, SGTP_EINVAL, "unknown workspace tensor");
     }
-    MCHK(m, hipMemcpyAsync(dst, src, row * m->last_B, hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    static_assert(D_OUTP == D_H, "every blocked tensor has 256 columns");
+    const long long n = (long long)m->last_B * D_H;
+    hipLaunchKernelGGL(k_unblock, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, blk, D_H, m->last_B, (bf16 *)dst);
+    MCHK(m, hipGetLastError());
     return SGTP_OK;
 }
 
@@ -1143,19 +1263,14 @@ int sgtp_mlp_train_step_sampled(sgtp_mlp *m, const float *X_all, const float *U_
     hipStream_t st = (hipStream_t)stream;
     m->last_sampled = true;
     const AdamArgs ad = adam_args(m, lr, beta1, beta2, eps);
-    bool counted = false;
-    if (int rc = grad_rows(m, RowSrc{X_all, U_all, M, (uint32_t)seed, (uint32_t)(seed >> 32)}, B, N, sig_a, sig_d,
-                           loss, nullptr, st, &ad, &counted))
-        return rc;
-    if (!counted) hipLaunchKernelGGL(k_step_count, dim3(1), dim3(64), 0, st, m->adam_t);
-    MCHK(m, hipGetLastError());
-    return SGTP_OK;
+    return grad_rows(m, RowSrc{X_all, U_all, M, (uint32_t)seed, (uint32_t)(seed >> 32)}, B, N, sig_a, sig_d, loss,
+                     nullptr, st, &ad);
 }
 
 int sgtp_gemm_bf16(const void *A, long long a_m, long long a_k, const void *B, long long b_k, long long b_n, int M,
                    int N, int K, const float *bias, float *C, long long ldc, void *stream) {
     if (!A || !B || !C || M < 1 || N < 1 || K < 1) return SGTP_EINVAL;
-    gemm((hipStream_t)stream, (const bf16 *)A, a_m, a_k, (const bf16 *)B, b_k, b_n, M, N, K, bias, C, ldc, nullptr, 0);
+    gemm((hipStream_t)stream, (const bf16 *)A, a_m, a_k, (const bf16 *)B, b_k, b_n, M, N, K, bias, C, ldc);
     return hipGetLastError() == hipSuccess ? SGTP_OK : SGTP_EDEVICE;
 }
 
