@@ -35,7 +35,7 @@ PEAK_FP32_TFLOPS = 157.3  # MI355X published FP32 vector peak
 # (one counter group per run; commands and tables in profiles/sweep_<W>_counters.md):
 # c4 k_sweep<0, 3, 9, 0, 1, 0> (one workgroup per tile of 2 x 256 samples), c3 the same
 # kernel with one sample per lane and k_sweep_persistent<0, 3, 9> (one record per schedule),
-# c2 k_sweep<0, 3, 3, 6, 1, 1> (split variant).  HBM bytes =
+# c2 k_sweep<0, 3, 3, 6, 1, 1> (128 samples per workgroup).  HBM bytes =
 # 2.000 x FETCH_SIZE + 1.000 x WRITE_SIZE (KiB), the factors being 256 MiB over what each
 # counter reads for the 256 MiB elementwise copy of the same runs (131087.5-131091.5 KiB
 # fetched, 262144 KiB written).  FP32 FLOPs = 64 x SQ_INSTS_VALU_FLOPS_FP32, which counts ADD + MUL +
@@ -245,7 +245,7 @@ def mfma_block(mlp, data, params) -> dict:
         ms = _events_ms(lambda: mlp.forward(X, out=Y), 20)
         fl = rows * 2.0 * (50 * 256 + 256 * 256 + 256 * 200)
         fwd[str(rows)] = {"ms": ms, "tflops": fl / ms / 1e9, "mfma_frac": fl / ms / 1e9 / PEAK_BF16_TFLOPS,
-                          "kernel": "fused three-layer" if rows <= 4096 else "tiled products"}
+                          "kernel": "fused three-layer" if rows <= 4096 else "fused three-layer, wide"}
     out["forward"] = fwd
     return out
 
