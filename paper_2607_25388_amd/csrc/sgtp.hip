@@ -805,9 +805,11 @@ __device__ __forceinline__ Foot project_ahead(const float4 *__restrict__ nodes, 
             seg = min(seg + t, last);
         }
     }
-    if (__builtin_expect(t == 0 && g[0] < 0.0f, 0)) {  // (no move forward: the whole budget is left)
+    // no move forward (told by the segment itself: a later batch may well have ended with t = 0,
+    // and at the window's end t > 0 moves nothing): the whole budget is left
+    if (__builtin_expect(seg == seg0 && g[0] < 0.0f, 0)) {
         float g0 = g[0];
-        for (int moves = seg - seg0; moves < max_moves && seg > 0 && g0 < 0.0f; ++moves) {
+        for (int moves = 0; moves < max_moves && seg > 0 && g0 < 0.0f; ++moves) {
             --seg;
             g0 = ahead_of(nodes[2 * seg], X, Y);
         }
