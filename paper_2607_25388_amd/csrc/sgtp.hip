@@ -1374,11 +1374,16 @@ __device__ __forceinline__ SampleResult lane_sample(const KParams &P_in, const B
 // scoring wave from the stages' velocities (shorter streams, but one more hand-over per step:
 // mid-scale race +3 %).
 // ------------------------------------------------------------------------------
-// The LDS accesses of one wave are carried out in the order in which it issues them, so a
+// Progress counters in LDS, read and written by different waves.  Their pointers carry the LDS
+// address space: a volatile access through a generic pointer stays a FLAT instruction, which
+// shares the order of the DS instructions on the slots only where a wait separates the two.
+// The DS instructions of one wave are carried out in the order in which it issues them, so a
 // counter written after its slot is seen after the slot, and a slot read before its counter
-// is written was read before: between waves of a workgroup that exchange through LDS alone
-// the compiler's order is all that is needed (a workgroup fence would also wait for every
-// access in flight, at each counter).
+// is written was read before: between waves of a workgroup that exchange through DS
+// instructions alone the compiler's order is all that is needed (a workgroup fence would also
+// wait for every access in flight, at each counter).
+typedef volatile int __attribute__((address_space(3))) *lds_counters;
+__device__ __forceinline__ lds_counters counters_at(char *lds, int offset) { return (lds_counters)(lds + offset); }
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
 template <int MODEL, int NDISC, int MAXOPP, int NPF>
@@ -1395,7 +1400,7 @@ __device__ __forceinline__ SampleResult lane_sample_team(const KParams &P, const
     const int i = team_sample<MODEL>(threadIdx.x);
     float2 *uring = (float2 *)(lds + L.sp_uring);  // [TEAM_RING][TEAM]: controls of the step
     float4 *sring = (float4 *)(lds + L.sp_sring);  // [TEAM_RING][TEAM]: X, Y, PSI, VX after the step
-    volatile int *sync = (volatile int *)(lds + L.sp_sync);
+    const lds_counters sync = counters_at(lds, L.sp_sync);
     float *fin = (float *)(lds + L.sp_fin);        // [TF_* rows][TEAM]
     const int N = bs.N;
     if (threadIdx.x < TS_WORDS) sync[threadIdx.x] = 0;
@@ -1667,7 +1672,7 @@ __device__ void reroll_block(const KParams &P, const LdsLayout &L, const BlockSt
     // its dynamics (which do not need it); prog[piece] counts the states written
     const bool proj_lane = tid >= 64 && tid < 64 + nch;
     const int pch = tid - 64;
-    volatile int *prog = (volatile int *)(lds + L.rr_sync);
+    const lds_counters prog = counters_at(lds, L.rr_sync);
     float st[6] = {0.0f, 0.0f, 0.0f, bs.vx0, bs.vy0, bs.om0};
     int seg = NPF == 0 ? 32 * bs.seg0 : bs.seg0;  // (as the sample's lane counts it)
     if (chunk_lane && ch > 0) {
@@ -1896,7 +1901,7 @@ __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int it
             }
         } else if (SPL) {
             // the scoring wave names its best sample; the lanes that hold its parts export them
-            volatile int *best = (volatile int *)(lds + A.L.sp_sync) + TS_BEST;
+            const lds_counters best = counters_at(lds, A.L.sp_sync) + TS_BEST;
             const unsigned long long b = __ballot(valid && scoring && key == wmin);
             if (scoring && lane == 0) *best = b ? __builtin_ctzll(b) : -1;
             __syncthreads();
