@@ -262,9 +262,17 @@ __device__ __forceinline__ void load_tile(const bf16 *__restrict__ P, long long 
             v[i] = *(const u16x8_any *)p;
         } else {
             u16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
+            if constexpr (VK) {
+                if (r < R && k < K) {  // (a row beyond the product skips the eight tests)
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (VK ? r < R && k + j < K : k < K && r + j < R) x[j] = __builtin_bit_cast(unsigned short, p[j]);
+                    for (int j = 0; j < 8; ++j)
+                        if (k + j < K) x[j] = __builtin_bit_cast(unsigned short, p[j]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k < K && r + j < R) x[j] = __builtin_bit_cast(unsigned short, p[j]);
+            }
             v[i] = x;
         }
     }
@@ -986,8 +994,10 @@ void gemm(hipStream_t st, const bf16 *A, long long a_m, long long a_k, const bf1
                stage_mode(A, a_m, a_k), stage_mode(B, b_n, b_k), -1};
     // Large tiles wherever each operand has a unit stride (any alignment).  256 x 256 where
     // those tiles fill the CUs (their MFMAs per LDS byte are twice the smaller ones': 16384 x
-    // 1024 x 1024 51 us against 67), 128 x 128 otherwise (2048^3 34 against 76, 8192 x 512 x
-    // 512 14 against 28).  The 64 x 64 kernel took 199, 116 and 35 us for these.
+    // 1024 x 1024 42-48 us by layout against 67), 128 x 128 otherwise, down to the smallest sizes:
+    // 2048^3 31-34 us, 512^3 9-10, 64 x 64 x 4096 51-83, 64^3 and 1 x 1 x 1 about 4.  The 64 x 64
+    // kernel took 114-282, 68-157, 11-17, 62-109 and about 5 us for these; it serves operands
+    // without a unit stride.
     const bool ak = a_k == 1, bk = b_k == 1;
     if ((ak || a_m == 1) && (bk || b_n == 1)) {
         const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
