@@ -72,6 +72,25 @@ def test_teams_match_one_lane(planner, model, name, agent, K, N):
     assert planner.status() == 0
 
 
+@pytest.mark.parametrize("model,n,N,n_disc,variant", [(0, 2, 40, 1, PAIR), (0, 2, 20, 3, PAIR), (0, 4, 25, 3, PAIR),
+                                                      (0, 1, 30, 1, PAIR), (1, 2, 40, 1, ONE), (1, 4, 25, 3, ONE),
+                                                      (0, 6, 20, 1, ONE)])
+def test_fallback_where_the_rings_do_not_fit(planner, model, n, N, n_disc, variant):
+    """4 cm nodes and 80 moves a step make the staged window 1536 rows (48 KiB): with the teams' rings
+    (8.2 KB and more) the tables no longer fit in 58 KiB of LDS, without them they do.  The plan is
+    built again without teams: a pair of lanes per sample for the dynamic model and at most three
+    opponents, one lane (the kernel that reads rows ahead) otherwise."""
+    track = inputs.make_fourier_track(300.0, 10.0, 1000, ds=0.04)
+    race = inputs.make_race(track, n, N, 10.0, False, 3001, 2001)
+    params = dict(inputs.default_params(N, n_disc), model=model, max_moves=80)
+    K = 1100
+    for agent in {0, n - 1}:
+        small, large = _both(planner, track, race, params, K, variant, agent)
+        _same_bits(small, large, K)
+    r = PY.oracle_for(track, params).rollout_cost(race, n - 1, 1, K)
+    PY.check_choice(small["choice"], r, params, f"fallback {model} {n} {N}")
+
+
 @pytest.mark.parametrize("model", [0, 1])
 @pytest.mark.parametrize("fine", [False, True])
 def test_tight_corners_and_samples_far_inside(planner, model, fine):
