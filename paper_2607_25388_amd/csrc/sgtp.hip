@@ -2011,50 +2011,65 @@ __device__ __forceinline__ void sweep_tile(const LaunchArgs &A, int tile, int it
         float *sums = (float *)(lds + A.L.rr_u);  // [2N + 1]: sum of weights, weighted controls
         const float *pp = A.pi_part + (size_t)t0 * pstride;
         float Smin = INFINITY;
-        for (int t = lane; t < n_tiles_item; t += 64) Smin = fminf(Smin, pp[(size_t)t * pstride]);
+        constexpr int SB = SPL ? 4 : 1;  // scores of a lane read together
+        for (int t = lane; t < n_tiles_item; t += 64 * SB) {
+            float Sp[SB];
+#pragma unroll
+            for (int j = 0; j < SB; ++j) Sp[j] = pp[(size_t)min(t + 64 * j, n_tiles_item - 1) * pstride];
+#pragma unroll
+            for (int j = 0; j < SB; ++j) Smin = fminf(Smin, Sp[j]);
+        }
         Smin = wave_min_f32(Smin);
         pi_min = Smin;
         if (Smin < INFINITY) {
-            if ((int)threadIdx.x < 2 * bs.N + 1) {
-                // teams: partials of pi_teams x 64 samples are formed first, then added in order
-                // like the others; read PB at a time (one by one, the 329 teams of 21000 samples
-                // took 0.04 ms per sweep longer)
-                constexpr int PB = 8;
-                const float *pc = pp + 1 + threadIdx.x;
-                float v = 0.0f;
-                auto add = [&](auto n_, const float *Sp, const float *vp) {
-                    constexpr int n = decltype(n_)::value;
+            const bool col = (int)threadIdx.x < 2 * bs.N + 1;
+            const float *pc = pp + 1 + threadIdx.x;
+            float v = 0.0f;
+            if constexpr (SPL != 0) {
+                // partials of pi_teams x 64 samples are formed first, then added in order like the
+                // others.  The two weights of a team (against its partial sum's reference, and of
+                // that against the smallest) are the same for every column: each thread forms
+                // those of one team.  Formed by every column for itself, three exponentials for
+                // two teams, they were most of this loop: 65536 samples of 12 steps 189 us a call, now
+                // 139, of 40 steps 288 -> 234 (two waves per 64 samples: 174 and 344)
+                float2 *wt = (float2 *)(lds + A.L.sp_sring);  // [BLOCK] (the rings are used; < 0: no weight)
+                constexpr int PB = 32;
+                for (int b0 = 0; b0 < n_tiles_item; b0 += BLOCK) {
+                    const int m = min(BLOCK, n_tiles_item - b0);
+                    const float Sp = (int)threadIdx.x < m ? pp[(size_t)(b0 + threadIdx.x) * pstride] : INFINITY;
+                    float St = fminf(Sp, __shfl_xor(Sp, 1));
+                    if (A.pi_teams != 2) St = fminf(St, __shfl_xor(St, 2));
+                    if (b0 > 0) __syncthreads();
+                    wt[threadIdx.x] = make_float2(Sp < INFINITY ? expf((St - Sp) * A.P.inv_lambda) : -1.0f,
+                                                  St < INFINITY ? expf((Smin - St) * A.P.inv_lambda) : -1.0f);
+                    __syncthreads();
+                    if (!col) continue;
+                    auto add = [&](auto n_, int t) {  // teams t .. t + PB - 1, read together
+                        constexpr int n = decltype(n_)::value;
+                        float vp[PB];
 #pragma unroll
-                    for (int g = 0; g < PB; g += n) {
-                        float St = Sp[g], vt = 0.0f;
+                        for (int j = 0; j < PB; ++j) vp[j] = pc[(size_t)(b0 + min(t + j, m - 1)) * pstride];
 #pragma unroll
-                        for (int j = 1; j < n; ++j) St = fminf(St, Sp[g + j]);
+                        for (int g = 0; g < PB; g += n) {
+                            float vt = 0.0f;
 #pragma unroll
-                        for (int j = 0; j < n; ++j)
-                            if (Sp[g + j] < INFINITY) vt += vp[g + j] * expf((St - Sp[g + j]) * A.P.inv_lambda);
-                        if (St < INFINITY) v += vt * expf((Smin - St) * A.P.inv_lambda);
-                    }
-                };
-                if (!SPL)
-                    for (int t = 0; t < n_tiles_item; ++t) {
-                        const float St = pp[(size_t)t * pstride];
-                        if (St < INFINITY) v += pc[(size_t)t * pstride] * expf((Smin - St) * A.P.inv_lambda);
-                    }
-                for (int t = 0; SPL && t < n_tiles_item; t += PB) {
-                    float Sp[PB], vp[PB];
-#pragma unroll
-                    for (int j = 0; j < PB; ++j) {
-                        const size_t o = (size_t)min(t + j, n_tiles_item - 1) * pstride;
-                        Sp[j] = pp[o];
-                        vp[j] = pc[o];
-                    }
-#pragma unroll
-                    for (int j = 0; j < PB; ++j) Sp[j] = t + j < n_tiles_item ? Sp[j] : INFINITY;
-                    if (A.pi_teams == 2) add(std::integral_constant<int, 2>{}, Sp, vp);
-                    else add(std::integral_constant<int, 4>{}, Sp, vp);
+                            for (int j = g; j < g + n; ++j)
+                                if (wt[t + j].x >= 0.0f) vt += vp[j] * wt[t + j].x;
+                            if (wt[t + g].y >= 0.0f) v += vt * wt[t + g].y;
+                        }
+                    };
+                    if (A.pi_teams == 2)
+                        for (int t = 0; t < m; t += PB) add(std::integral_constant<int, 2>{}, t);
+                    else
+                        for (int t = 0; t < m; t += PB) add(std::integral_constant<int, 4>{}, t);
                 }
-                sums[threadIdx.x] = v;
+            } else if (col) {
+                for (int t = 0; t < n_tiles_item; ++t) {
+                    const float St = pp[(size_t)t * pstride];
+                    if (St < INFINITY) v += pc[(size_t)t * pstride] * expf((Smin - St) * A.P.inv_lambda);
+                }
             }
+            if (col) sums[threadIdx.x] = v;
             __syncthreads();
             float *ub = (float *)(lds + A.L.ubar);
             if ((int)threadIdx.x < 2 * bs.N) ub[threadIdx.x] = sums[1 + threadIdx.x] / sums[0];
