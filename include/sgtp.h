@@ -226,13 +226,14 @@ int sgtp_advance(sgtp_ctx *ctx, const sgtp_params *p, const sgtp_race *races, in
  * output arrays, uploads their descriptors once and runs Alg. 1 for all races per
  * call: one setup launch, then one sweep launch per phase covering every vehicle
  * of every race.  Tiles of BLOCK = 256 samples (x samples_per_lane) are the unit
- * of work; a sweep over at most 65536 samples (49152 with more than 3 opponents; one
- * sample per lane) runs 64-sample tiles whose work is dealt out to the four waves of
- * a workgroup (dynamics on two; perturbation and cost terms; projection, opponents
- * and scoring), or, where those LDS rings do not fit, with each sample on a pair of
- * lanes (dynamic model, feasibility selection, at most 32768 samples and 3
- * opponents); such sweeps run one workgroup per tile (persistent is ignored; the
- * extra ego response takes this form by its own sample count).  Every variant gives
+ * of work.  A sweep over at most 65536 samples (49152 with more than 3 opponents, or
+ * fewer where their tables leave LDS for two teams per CU; one sample per lane) runs
+ * one workgroup per tile (persistent is ignored; the extra ego response takes this form
+ * by its own sample count).  Unless its horizon is too short for its samples, its tiles
+ * are of 64 samples whose work is dealt out to the four waves of a workgroup (dynamics
+ * on two; perturbation and cost terms; projection, opponents and scoring), or, where
+ * those LDS rings do not fit, each sample runs on a pair of lanes (dynamic model,
+ * feasibility selection, at most 32768 samples and 3 opponents).  Every variant gives
  * the same per-sample bits.  A
  * persistent sweep keeps a fixed grid of workgroups that pull chunks of
  * tiles from 8 queues (vehicles assigned longest-first; a workgroup serves its own

@@ -2889,6 +2889,7 @@ struct Plan {  // host image of one launch sequence's descriptors
     // per list: the team variant, and the samples per tile (TEAM, or BLOCK x samples per lane /
     // lanes per sample)
     int team_all = 0, team_ego = 0, team_one = 0;
+    int small_all = 0, small_ego = 0;  // few enough samples for teams: one workgroup per tile
     int pi_teams = 4;
     long long pi_all = 0;  // samples of all vehicles
     int tile_all = 0, tile_ego = 0, tile_one = 0;
@@ -2898,43 +2899,77 @@ LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc, bool setup = false)
 int maxopp_bucket(int n_opp);
 constexpr int LDS_BUDGET = 58 * 1024;
 
-// Whether a launch over `samples` samples (its list's; `all`: every vehicle's) takes the team
-// variant: it is the faster one until the chip is full with one lane per sample.
-bool team_list(int nopp, long long samples) {
-    // up to the teams that are resident at once: four per CU (registers), three with the
-    // wider tables of more than 3 opponents (LDS).  One team more than that and a second
-    // round begins (10 vehicles, 65536 samples of the ego: 0.19 against 0.16 ms; 4 vehicles,
-    // 131072 samples: 0.29 against 0.17 ms).  Planning step with two waves per 64 samples, or
-    // one lane per sample beyond 3 opponents, before and now: 3 vehicles at K = 128 (N = 12)
-    // 0.172 -> 0.126 ms, 2 at 1024 (N = 20) 0.259 -> 0.201, 3 at 16384 (N = 40) 0.651 ->
-    // 0.576, 3 at 21800 (N = 40) 0.577 -> 0.396 (L = 2), 10 at 4000 (N = 40) 0.607 -> 0.379
-    // (L = 2); 126 games of 3 at K = 128 0.367 -> 0.230 ms.
-    return samples <= (nopp <= 3 ? TEAM_MAX_SAMPLES : TEAM_MAX_SAMPLES_WIDE);
+// Samples in a list (all vehicles, the egos, or one vehicle) up to which it runs as teams of 64: the
+// teams that are resident at once, four per CU (registers), three with the wider tables of more
+// than 3 opponents, two where these tables leave LDS for no more.  One team more and a second
+// round begins.  Beyond 3 opponents that loses to one lane per sample: 10 vehicles, 65536 samples of
+// the ego 0.19 against 0.16 ms a sweep; 16 vehicles, 50 steps, two teams per CU, 32768 samples of one
+// vehicle 191 against 209 us, 32832 262 against 209.  Up to 3 opponents the sums of both kinds are
+// shorter and a second round at two teams per CU still wins (2 vehicles, 0.1 m nodes, 33280 samples
+// 482 us a planning step against 526) or draws level (65536: 555 against 548).  4 vehicles, 131072
+// samples: 0.29 against 0.17 ms.
+long long team_samples_max(int nopp, long long wide_max) { return nopp <= 3 ? TEAM_MAX_SAMPLES : wide_max; }
+long long team_samples_lds(int total_team) {
+    constexpr int CUS = 256, LDS_CU = 160 * 1024, GRANULE = 1280, STATIC = 16;
+    const long long per_cu = LDS_CU / ((total_team + STATIC + GRANULE - 1) / GRANULE * GRANULE);
+    return std::min(TEAM_MAX_SAMPLES_WIDE, per_cu * CUS * TEAM);
+}
+
+// A list of one launch, as its variant is chosen: teams, and the sum of their horizons.
+struct ListSize {
+    long long samples = 0, teams = 0, team_steps = 0;
+    void add(long long K, long long n, long long N) {
+        const long long t = n * ((K + TEAM - 1) / TEAM);
+        samples += n * K;
+        teams += t;
+        team_steps += t * N;
+    }
+};
+
+// Whether a small list runs as teams.  A team saves time in every step (about 1 us with the dynamic
+// model, 0.6 with the kinematic one) and costs some in every workgroup (staging, hand-off, three
+// contended atomics for 64 samples instead of nine for 256; with per-sample outputs all of a team's
+// are written by one wave), so the horizon decides.  Planning step of L = 1, one lane per sample
+// against teams: 10 vehicles at K = 4000, dynamic, N = 4 102 us against 105, N = 6 119 / 112, N = 12
+// 163 / 141; 3 at 16384 N = 4 104 / 111, N = 6 117 / 115; 126 games of 3 at K = 128, N = 4 125 / 135,
+// N = 8 154 / 149, kinematic N = 8 129 / 137, N = 12 149 / 148.  One call with outputs, 32768
+// samples: dynamic N = 5 54 / 59, N = 12 74 / 70; kinematic N = 12 60 / 63, N = 20 73 / 72.  Longer
+// horizons: 3 vehicles at K = 128 (N = 12) 0.172 (two waves per 64 samples) -> 0.119 ms, 2 at 1024
+// (N = 20, direct calls) 0.259 -> 0.207, 3 at 16384 (N = 40) 0.651 -> 0.574, 10 at 4000 (N = 40, L = 2)
+// 0.574 (one lane per sample) -> 0.403.  The path-integral sums of up to 3 opponents are taken
+// over 128 samples, which only teams do.
+bool team_list(const sgtp_params *p, int nopp, const ListSize &l, bool outputs) {
+    if (p->update == 1 && nopp <= 3) return true;
+    const int per_step = (p->model == 0 ? (p->update == 1 ? 256 : outputs ? 64 : 128) : (outputs ? 32 : 80));
+    return l.teams * l.teams <= per_step * l.team_steps;
 }
 
 int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_races, int spl, Plan &pl,
-                    int one_agent, bool allow_team, bool ctx_limits) {
+                    int one_agent, bool allow_team, long long wide_max, bool ctx_limits) {
     if (!races || n_races < 1) return fail(c, SGTP_EINVAL, "no races");
     if (ctx_limits && n_races > c->max_races) return fail(c, SGTP_ESHAPE, "n_races exceeds the context");
     {
-        long long all = 0, ego = 0;
+        ListSize all, ego, one;
         int nopp = 0;
         for (int r = 0; r < n_races; ++r) {
-            const long long K = std::max(races[r].K, 0);
-            all += K * std::max(races[r].n_agents, 0);
-            ego += K;
+            const long long K = std::max(races[r].K, 0), N = std::max(races[r].N, 0);
+            all.add(K, std::max(races[r].n_agents, 0), N);
+            ego.add(K, 1, N);
+            if (r == 0) one.add(K, 1, N);
             nopp = std::max(nopp, races[r].n_agents - 1);
         }
-        const long long one = std::max(races[0].K, 0);
-        const bool team = allow_team && spl == 1;
-        pl.team_all = team && team_list(nopp, all);
-        pl.team_ego = team && team_list(nopp, ego);
-        pl.team_one = team && team_list(nopp, one);
+        const long long most = allow_team && spl == 1 ? team_samples_max(nopp, TEAM_MAX_SAMPLES_WIDE) : -1;
+        const long long teams = std::min(most, team_samples_max(nopp, wide_max));
+        pl.small_all = all.samples <= most;
+        pl.small_ego = ego.samples <= most;
+        pl.team_all = all.samples <= teams && team_list(p, nopp, all, false);
+        pl.team_ego = ego.samples <= teams && team_list(p, nopp, ego, false);
+        pl.team_one = one.samples <= teams && team_list(p, nopp, one, true);
         // where the team's rings do not fit in LDS: a pair of lanes per sample up to about one
         // wave per SIMD (dynamic model, feasibility selection, at most 3 opponents)
         pl.lps = (!allow_team && spl == 1 && p->model == 0 && p->update == 0 && nopp <= 3 &&
-                  all <= LPS2_MAX_SAMPLES) ? 2 : 1;
-        pl.pi_all = all;
+                  all.samples <= LPS2_MAX_SAMPLES) ? 2 : 1;
+        pl.pi_all = all.samples;
         pl.tile_all = pl.team_all ? TEAM : BLOCK * spl / pl.lps;
         pl.tile_ego = pl.team_ego ? TEAM : BLOCK * spl / pl.lps;
         pl.tile_one = pl.team_one ? TEAM : BLOCK * spl / pl.lps;
@@ -3009,10 +3044,11 @@ int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, i
     return SGTP_OK;
 }
 
-// The plan of one launch sequence; the team variant only where its LDS rings fit.
+// The plan of one launch sequence; the team variant only where its LDS rings fit, and beyond 3
+// opponents only up to the teams that LDS keeps resident.
 int build_plan(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_races, int spl, Plan &pl,
                int one_agent = -1, bool ctx_limits = true) {
-    int rc = build_plan_once(c, p, races, n_races, spl, pl, one_agent, true, ctx_limits);
+    int rc = build_plan_once(c, p, races, n_races, spl, pl, one_agent, true, TEAM_MAX_SAMPLES_WIDE, ctx_limits);
     // The order of the path-integral sums is part of their result: partial sums over 128
     // samples up to PI_128_MAX_SAMPLES and 3 opponents (where tables of this many bytes fit),
     // over BLOCK samples otherwise.
@@ -3021,11 +3057,13 @@ int build_plan(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, int n_
     const bool by_128 = !rc && pl.pi_all <= PI_128_MAX_SAMPLES && pl.n_opp_max <= 3 &&
                         make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc, true).total + PI_128_BYTES <= LDS_BUDGET;
     pl.pi_teams = by_128 ? 2 : 4;
-    if (rc || !(pl.team_all || pl.team_ego || pl.team_one) ||
-        make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc).total_team <= LDS_BUDGET)
-        return rc;
+    if (rc || !(pl.team_all || pl.team_ego || pl.team_one)) return rc;
+    const int total = make_layout(pl, maxopp_bucket(pl.n_opp_max), p->n_disc).total_team;
+    const bool fits = total <= LDS_BUDGET;
+    const long long wide_max = team_samples_lds(total);
+    if (fits && (pl.n_opp_max <= 3 || wide_max >= TEAM_MAX_SAMPLES_WIDE)) return rc;
     pl = Plan();
-    return build_plan_once(c, p, races, n_races, spl, pl, one_agent, false, ctx_limits);
+    return build_plan_once(c, p, races, n_races, spl, pl, one_agent, fits, wide_max, ctx_limits);
 }
 
 LdsLayout make_layout(const Plan &pl, int maxopp, int ndisc, bool setup) {
@@ -3403,7 +3441,8 @@ int plan_enqueue(sgtp_plan *P, hipStream_t st) {
             w.q_begin[q] = ego ? P->qb_ego[q] : P->qb_all[q];
             w.q_len[q] = ego ? P->ql_ego[q] : P->ql_all[q];
         }
-        const int grid = P->opt.persistent && !w.team ? (ego ? P->grid_ego : P->grid_all) : 0;
+        const bool small = ego ? P->pl.small_ego : P->pl.small_all;
+        const int grid = P->opt.persistent && !small ? (ego ? P->grid_ego : P->grid_all) : 0;
         const bool timed = c->timing && !P->capturing;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) {
@@ -3765,8 +3804,8 @@ int sgtp_plan_create(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, 
         delete P;
         return rc;
     }
-    // the pair and team variants run one workgroup per tile
-    if (P->pl.lps == 2 || P->pl.team_all) P->opt.persistent = o.persistent = 0;
+    // the pair variant and small lists run one workgroup per tile
+    if (P->pl.lps == 2 || P->pl.small_all) P->opt.persistent = o.persistent = 0;
     layout_queues(P->pl, P->pl.all, P->pl.tile_all, P->qb_all, P->ql_all);
     layout_queues(P->pl, P->pl.ego, P->pl.tile_ego, P->qb_ego, P->ql_ego);
     P->pl.tiles_all = P->ql_all[NQ - 1] + P->qb_all[NQ - 1];
