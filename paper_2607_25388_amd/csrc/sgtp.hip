@@ -1816,10 +1816,16 @@ __device__ __forceinline__ void pi_accumulate(const KParams &P, const BlockState
     a.c1 *= fa;
     const float2 *ubar = (const float2 *)(lds + L.ubar);
     // the loop's parameters in vector registers: in scalar ones they were spilled and reloaded
-    // at every step pair where the workgroup also holds its queue's state
+    // at every step pair where the workgroup also holds its queue's state.  (Copied here, by way of
+    // an opaque scalar: the copies moved in front of the sample loop otherwise and were spilled
+    // around it, 12 to 28 bytes a lane also where no path integral is asked for.)
+    auto here = [](float x) {
+        asm volatile("" : "+s"(x));
+        return vreg(x);
+    };
     KParams Q = P;
-    Q.sigma_a = vreg(P.sigma_a); Q.sigma_d = vreg(P.sigma_d);
-    Q.a_min = vreg(P.a_min); Q.a_max = vreg(P.a_max); Q.d_min = vreg(P.d_min); Q.d_max = vreg(P.d_max);
+    Q.sigma_a = here(P.sigma_a); Q.sigma_d = here(P.sigma_d);
+    Q.a_min = here(P.a_min); Q.a_max = here(P.a_max); Q.d_min = here(P.d_min); Q.d_max = here(P.d_max);
     const PhiloxLane pl = philox_lane(k, bs.ctr2, bs.ctr3, bs.key0, bs.key1);
     for (int next = m0; 2 * next < bs.N;) {
         const int m = __builtin_amdgcn_readfirstlane(next);
