@@ -3155,8 +3155,11 @@ void launch_sweep_t(const LaunchArgs &A, int grid, hipStream_t st, int *occ) {
             n = 1;
         *occ = n;
     } else if (grid == 0) {
-        // about one wave per SIMD or fewer (small games): the latency variant reads ahead
-        constexpr int LAT_WAVES = 1536;
+        // one wave per SIMD or fewer: the latency variant reads ahead.  Where two of its waves share
+        // a SIMD the throughput variant's shorter step wins: 4 vehicles, 32976 samples of 50 steps,
+        // two per lane, 260 workgroups 554 against 512 us a planning step, of 20 steps 252 / 235;
+        // 256 workgroups 490 (the earlier, longer step's line was at 1536 waves)
+        constexpr int LAT_WAVES = 1024;
         if (A.team)
             hipLaunchKernelGGL((k_sweep<MODEL, NDISC, MAXOPP, 6, 1, 1>), dim3(A.n_tiles), dim3(BLOCK),
                                A.L.total_team, st, A);

@@ -78,3 +78,22 @@ def test_path_integral_of_few_opponents_stays_with_teams(planner, K):
     plan, _ = _plan(planner, track, [inputs.make_race(track, 1, 2, 8.0, False, 3000, 2000)], params, K, sg.plan_options())
     assert plan.info()["tiles"] == -(-K // TEAM)
     plan.close()
+
+
+@pytest.mark.parametrize("model,K", [(0, 32768), (0, 32769), (0, 49153), (1, 32769)])
+def test_two_samples_per_lane_around_one_wave_per_simd(planner, model, K):
+    """256 workgroups read ahead, 260 do not: the same choices as one sample per lane."""
+    import torch
+    import paper_2607_25388_amd.sgtp as sg
+    track = inputs.make_fourier_track(300.0, 10.0, 1000)
+    params = dict(inputs.default_params(12, 1), model=model)
+    race = inputs.make_race(track, 4, 12, 8.0, True, 3000, 2000)
+    out = []
+    for spl in (1, 2):
+        plan, rts = _plan(planner, track, [race], params, K, sg.plan_options(persistent=0, samples_per_lane=spl))
+        plan.run()
+        u = plan.run()
+        torch.cuda.synchronize()
+        out.append((plan.choices().tobytes(), u.cpu().numpy().tobytes(), rts[0].u_nom.cpu().numpy().tobytes()))
+        plan.close()
+    assert out[0] == out[1]
