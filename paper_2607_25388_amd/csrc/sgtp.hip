@@ -2125,6 +2125,24 @@ __global__ void __launch_bounds__(BLOCK, SPL || (NPF == 0 && LPS == 1) ? 4 : 1) 
     sweep_tile<MODEL, NDISC, MAXOPP, NPF, LPS, SPL>(A, tile, item, bs, lds, &s_last);
 }
 
+// The throughput sweep at five workgroups per CU: 96 VGPRs, which the kinematic model with a point
+// footprint and up to 3 opponents fits with one value spilled around the sample loop.  Its short
+// step leaves issue slots to a fifth wave: planning steps of 32 vehicles, 16384 samples (2048
+// workgroups), 8 steps 383 us with four and 330 with five, 12 steps 392 / 354, 40 steps 560 / 556; of
+// 96 vehicles at 8627, 12 steps 441 / 403, 40 steps 764 / 718.  Only beyond four per CU (768
+// workgroups, 40 steps: 291 / 298), and not for the path integral (1404 workgroups, 12 steps 376 / 409).
+constexpr int FIVE_PER_CU_TILES = 1024;
+template <int MODEL, int NDISC, int MAXOPP>
+__global__ void __launch_bounds__(BLOCK, 5) k_sweep5(LaunchArgs A) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ int s_last;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int item = find_item(A.items, A.n_items, tile);
+    BlockState bs;
+    stage_block<NDISC>(A, item, bs, lds);
+    sweep_tile<MODEL, NDISC, MAXOPP>(A, tile, item, bs, lds, &s_last);
+}
+
 // Persistent sweep: a fixed grid of workgroups pulls chunks of tiles from NQ queues
 // (its own first, then the others), restaging LDS only when the vehicle changes.
 // Every workgroup leaves once all queues are exhausted.
@@ -3184,8 +3202,15 @@ void launch_sweep_t(const LaunchArgs &A, int grid, hipStream_t st, int *occ) {
         else if (MAXOPP <= 3 && A.n_tiles * (BLOCK / 64) <= LAT_WAVES)
             hipLaunchKernelGGL((k_sweep<MODEL, NDISC, MAXOPP <= 3 ? MAXOPP : 3, 6>), dim3(A.n_tiles), dim3(BLOCK),
                                A.L.total, st, A);
-        else
+        else {
+            if constexpr (MODEL == 1 && NDISC == 1 && MAXOPP <= 3) {
+                if (A.n_tiles > FIVE_PER_CU_TILES && A.P.update == 0) {
+                    hipLaunchKernelGGL((k_sweep5<MODEL, NDISC, MAXOPP>), dim3(A.n_tiles), dim3(BLOCK), A.L.total, st, A);
+                    return;
+                }
+            }
             hipLaunchKernelGGL((k_sweep<MODEL, NDISC, MAXOPP>), dim3(A.n_tiles), dim3(BLOCK), A.L.total, st, A);
+        }
     } else {
         hipLaunchKernelGGL((k_sweep_persistent<MODEL, NDISC, MAXOPP>), dim3(grid), dim3(BLOCK), A.L.total, st, A);
     }

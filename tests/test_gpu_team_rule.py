@@ -97,3 +97,27 @@ def test_two_samples_per_lane_around_one_wave_per_simd(planner, model, K):
         out.append((plan.choices().tobytes(), u.cpu().numpy().tobytes(), rts[0].u_nom.cpu().numpy().tobytes()))
         plan.close()
     assert out[0] == out[1]
+
+
+@pytest.mark.parametrize("n,R,K", [(1, 1, 262144), (1, 1, 262145), (4, 8, 8300), (2, 9, 20000)])
+def test_kinematic_point_footprint_at_five_workgroups_per_cu(planner, n, R, K):
+    """Beyond 1024 workgroups the kernel with fewer registers runs: the bits of the persistent one."""
+    import torch
+    import paper_2607_25388_amd.sgtp as sg
+    track = inputs.make_fourier_track(300.0, 10.0, 1000)
+    params = dict(inputs.default_params(10, 1), model=1)
+    races = [inputs.make_race(track, n, 10, 8.0, n >= 4, 3000 + r, 2000 + r) for r in range(R)]
+    p = sg.Planner(max_agents_total=n * R, max_races=R, max_K=K)
+    try:
+        out = []
+        for persistent in (0, 1):
+            plan, rts = _plan(p, track, races, params, K, sg.plan_options(persistent=persistent))
+            assert plan.info()["tiles"] == n * R * -(-K // ONE)
+            plan.run()
+            u = plan.run()
+            torch.cuda.synchronize()
+            out.append([plan.choices().tobytes(), u.cpu().numpy().tobytes()] + [r.u_nom.cpu().numpy().tobytes() for r in rts])
+            plan.close()
+        assert out[0] == out[1]
+    finally:
+        p.close()
