@@ -668,7 +668,7 @@ __global__ void __launch_bounds__(64 * FWD_WAVES) k_mlp_fwd16(const float *X, in
 // permuted by the row).  The products are formed transposed, so that a lane holds four
 // consecutive columns of a row: 8-byte LDS and 16-byte global stores.  Same lane -> k map and
 // k order as k_mlp_fwd16, so the same bits.  Bound by the GELUs (two tanh per weight column
-// and row, about 40 instructions each) and the output's 52 MB: 65536 rows take 61 us (three
+// and row, about 40 instructions each) and the output's 52 MB: 65536 rows take 54 to 61 us (three
 // tiled products and a conversion: 231).
 constexpr int FWD_WIDE_WAVES = 8;
 __device__ __forceinline__ int act_piece(int row, int c) { return row * D_H + 8 * (c ^ (row & 15)); }

@@ -2934,10 +2934,10 @@ constexpr int LDS_BUDGET = 58 * 1024;
 // than 3 opponents, two where these tables leave LDS for no more.  One team more and a second
 // round begins.  Beyond 3 opponents that loses to one lane per sample: 10 vehicles, 65536 samples of
 // the ego 0.19 against 0.16 ms a sweep; 16 vehicles, 50 steps, two teams per CU, 32768 samples of one
-// vehicle 191 against 209 us, 32832 262 against 209.  Up to 3 opponents the sums of both kinds are
-// shorter and a second round at two teams per CU still wins (2 vehicles, 0.1 m nodes, 33280 samples
-// 482 us a planning step against 526) or draws level (65536: 555 against 548).  4 vehicles, 131072
-// samples: 0.29 against 0.17 ms.
+// vehicle 189 against 209 us, 32832 259 against 209.  Up to 3 opponents a second round at two teams
+// per CU still wins (2 vehicles, 0.1 m nodes, 33280 samples 482 us a planning step against 526) or
+// draws level (65536: 555 against 548); a fifth team per CU loses (4 vehicles, 131072 samples: 0.29
+// against 0.17 ms).
 long long team_samples_max(int nopp, long long wide_max) { return nopp <= 3 ? TEAM_MAX_SAMPLES : wide_max; }
 long long team_samples_lds(int total_team) {
     constexpr int CUS = 256, LDS_CU = 160 * 1024, GRANULE = 1280, STATIC = 16;
@@ -2966,11 +2966,12 @@ struct ListSize {
 // samples: dynamic N = 5 54 / 59, N = 12 74 / 70; kinematic N = 12 60 / 63, N = 20 73 / 72.  Longer
 // horizons: 3 vehicles at K = 128 (N = 12) 0.172 (two waves per 64 samples) -> 0.119 ms, 2 at 1024
 // (N = 20, direct calls) 0.259 -> 0.207, 3 at 16384 (N = 40) 0.651 -> 0.574, 10 at 4000 (N = 40, L = 2)
-// 0.574 (one lane per sample) -> 0.403.  The path-integral sums of up to 3 opponents are taken
-// over 128 samples, which only teams do.
+// 0.574 (one lane per sample) -> 0.403.  The path integral costs more per step in both kinds: 10
+// vehicles at 4000, N = 2 103 / 108, N = 4 125 / 119.  Its sums for up to 3 opponents are taken over
+// 128 samples, which only teams do.
 bool team_list(const sgtp_params *p, int nopp, const ListSize &l, bool outputs) {
     if (p->update == 1 && nopp <= 3) return true;
-    const int per_step = (p->model == 0 ? (p->update == 1 ? 256 : outputs ? 64 : 128) : (outputs ? 32 : 80));
+    const int per_step = (p->model == 0 ? (p->update == 1 ? 200 : outputs ? 64 : 128) : (outputs ? 32 : 80));
     return l.teams * l.teams <= per_step * l.team_steps;
 }
 
