@@ -2983,8 +2983,9 @@ int build_plan_once(sgtp_ctx *c, const sgtp_params *p, const sgtp_race *races, i
         ListSize all, ego, one;
         int nopp = 0;
         for (int r = 0; r < n_races; ++r) {
-            const long long K = std::max(races[r].K, 0), N = std::max(races[r].N, 0);
-            all.add(K, std::max(races[r].n_agents, 0), N);
+            // (checked race by race below; until then kept within what the sums hold)
+            const long long K = std::max(races[r].K, 0), N = std::min(std::max(races[r].N, 0), SGTP_MAX_N);
+            all.add(K, std::min(std::max(races[r].n_agents, 0), SGTP_MAX_AGENTS), N);
             ego.add(K, 1, N);
             if (r == 0) one.add(K, 1, N);
             nopp = std::max(nopp, races[r].n_agents - 1);
