@@ -42,7 +42,7 @@ PEAK_FP32_TFLOPS = 157.3  # MI355X published FP32 vector peak
 # TRANS + 2 FMA wave instructions (checked on the known-mix kernel of --counter-probe,
 # profiles/counter_probe_fp32.md).  They describe the kernel source with this SHA-256 and
 # the listed schedule fields only; anything else reports null.
-_SRC = "f407efbd0f459e02af1ecf9b547947cc6cdf9536c86071c9d2369012fb7a4097"
+_SRC = "b9938a1835ed6425891e8b385795f60dbaebc63c6485c8f31ddb2fae28ccf615"
 SWEEP_COUNTERS = {
     "c4": [{"source_sha256": _SRC, "hbm_bytes_per_launch": (16512.0 * 1.99972 + 118361.9) * 1024.0,
             "hw_fp32_flop_per_launch": 64 * 14103591713.0, "valu_wave_insts_per_launch": 13337103640.4,

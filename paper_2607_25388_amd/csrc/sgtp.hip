@@ -2364,6 +2364,9 @@ __global__ void __launch_bounds__(BLOCK) k_setup(LaunchArgs A, int w_limit, int 
             }
         }
         seg = block_argmin(best, bi);
+        // (a non-finite position has no nearest node: -1 wraps on a closed track; an open one's
+        // window starts at its first node, and a segment before it would be read from other tables)
+        if (seg < 0 && !T.closed) seg = 0;
     }
 
     // 2. unwrapped progress, frame and window extent
